@@ -234,32 +234,43 @@ hipError_t launch_update(const UpdLaunch& a, bool blocks) {
 }
 
 // ------------------------------------------------------------------ cosine
+// Pairs are taken in groups of consecutive ones that share A and its length (the
+// diagnostic's output cosines set one signal against every layer's gradient): a
+// workgroup loads its 4096 entries of A once and streams the group's B past them.
+constexpr int kCosBatch = kMaxMats;
 struct CosArgs {
-  const float* A[kUpdBatch];
-  const void* B[kUpdBatch];
-  int64_t numel[kUpdBatch];
-  int64_t blk0[kUpdBatch + 1];
+  const float* A[kCosBatch];      // per group
+  int64_t numel[kCosBatch];       // per group
+  int64_t gblk0[kCosBatch + 1];   // per group: first workgroup
+  int32_t first[kCosBatch + 1];   // per group: first pair
+  const void* B[kCosBatch];       // per pair
+  int64_t blk0[kCosBatch + 1];    // per pair: first block of partials
 };
 
-__global__ __launch_bounds__(256) void cosine_kernel(CosArgs a, int n, int b_bf16,
-                                                     double* __restrict__ part) {
-  __shared__ double red[16];
+// HBM bound: 4 or 8 bytes per element and pair. With A loaded per pair, 36 pairs
+// of 33.5M fp32 entries sharing A streamed 9.7 GB at 6.6 TB/s (1.46 ms); shared,
+// they stream 5.0 GB. The wave sums are parked in LDS, so the pair loop
+// has no barrier and the next pair's loads run during this pair's sums.
+template <bool B16>
+__global__ __launch_bounds__(256) void cosine_kernel(CosArgs a, int n, double* __restrict__ part) {
+  __shared__ double red[kCosBatch][3][4];
   const int64_t b = blockIdx.x;
-  const int m = find_mat(a.blk0, n, b);
-  const int64_t base = (b - a.blk0[m]) * kElemsPerBlock;
-  const int64_t end = (a.numel[m] < base + kElemsPerBlock) ? a.numel[m] : base + kElemsPerBlock;
-  const float* A = a.A[m];
-  const void* B = a.B[m];
+  const int g = find_mat(a.gblk0, n, b);
+  const int64_t lb = b - a.gblk0[g];
+  const int64_t base = lb * kElemsPerBlock;
+  const int64_t end = (a.numel[g] < base + kElemsPerBlock) ? a.numel[g] : base + kElemsPerBlock;
+  const float* A = a.A[g];
+  const int p0 = a.first[g], np = a.first[g + 1] - p0;
+  const int w = threadIdx.x >> 6;
   constexpr int U = kElemsPerBlock / 1024;
-  f32x4 xs[U], ys[U];
+  auto load_b = [&](int p, f32x4(&ys)[U]) {
+    const void* B = a.B[p];
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int64_t i = base + threadIdx.x * 4 + u * 1024;
-    xs[u] = ys[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (i < end) {
-      xs[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(A + i));
-      if (B) {
-        if (b_bf16) {
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = base + threadIdx.x * 4 + u * 1024;
+      ys[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (i < end && B) {
+        if constexpr (B16) {
           const u32x2 h = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>((const uint16_t*)B + i));
           ys[u] = f32x4{bf16_lo(h.x), bf16_hi(h.x), bf16_lo(h.y), bf16_hi(h.y)};
         } else {
@@ -267,22 +278,47 @@ __global__ __launch_bounds__(256) void cosine_kernel(CosArgs a, int n, int b_bf1
         }
       }
     }
-  }
-  float dt = 0.f, sa = 0.f, sb = 0.f;
+  };
+  f32x4 xs[U], ys[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const f32x4 x = xs[u], y = ys[u];  // zero outside the matrix
-    sa += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
-    dt += x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
-    sb += y.x * y.x + y.y * y.y + y.z * y.z + y.w * y.w;
+    const int64_t i = base + threadIdx.x * 4 + u * 1024;
+    xs[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (i < end) xs[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(A + i));
   }
-  const double d0 = block_sum_d((double)dt, red);
-  const double d1 = block_sum_d((double)sa, red);
-  const double d2 = block_sum_d((double)sb, red);
-  if (threadIdx.x == 0) {
-    part[3 * b] = d0;
-    part[3 * b + 1] = d1;
-    part[3 * b + 2] = d2;
+  load_b(p0, ys);
+  float sa = 0.f;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const f32x4 x = xs[u];  // zero outside the matrix
+    sa += x.x * x.x + x.y * x.y + x.z * x.z + x.w * x.w;
+  }
+  const double wa = wave_sum_d((double)sa);
+  for (int k = 0; k < np; ++k) {
+    f32x4 yn[U];
+    load_b(p0 + (k + 1 < np ? k + 1 : k), yn);
+    float dt = 0.f, sb = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const f32x4 x = xs[u], y = ys[u];
+      dt += x.x * y.x + x.y * y.y + x.z * y.z + x.w * y.w;
+      sb += y.x * y.x + y.y * y.y + y.z * y.z + y.w * y.w;
+    }
+    const double wd = wave_sum_d((double)dt), wb = wave_sum_d((double)sb);
+    if ((threadIdx.x & 63) == 0) {
+      red[k][0][w] = wd;
+      red[k][1][w] = wa;
+      red[k][2][w] = wb;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) ys[u] = yn[u];
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < 3 * np; q += 256) {
+    const int k = q / 3, j = q - 3 * k;
+    double s = 0.0;
+    for (int i = 0; i < 4; ++i) s += red[k][j][i];  // fixed order
+    part[3 * (a.blk0[p0 + k] + lb) + j] = s;
   }
 }
 
@@ -326,20 +362,41 @@ __global__ __launch_bounds__(256) void cosine_reduce_kernel(CosArgs a, const dou
 hipError_t launch_cosine(const CosLaunch& a) {
   hipStream_t st = (hipStream_t)a.stream;
   int64_t part_off = 0;
-  for (int m0 = 0; m0 < a.n; m0 += kUpdBatch) {
-    const int n = std::min(kUpdBatch, a.n - m0);
+  for (int m0 = 0; m0 < a.n; m0 += kCosBatch) {
+    const int n = std::min(kCosBatch, a.n - m0);
     CosArgs ca{};
-    int64_t nb = 0;
+    int64_t nb = 0, nwg = 0;
     for (int k = 0; k < n; ++k) {
-      ca.A[k] = a.A[m0 + k];
       ca.B[k] = a.B[m0 + k];
-      ca.numel[k] = a.numel[m0 + k];
       ca.blk0[k] = nb;
       nb += cosine_blocks(a.numel[m0 + k]);
     }
     ca.blk0[n] = nb;
-    FPO_LAUNCH("cosine", st,
-               cosine_kernel<<<dim3((unsigned)nb), dim3(256), 0, st>>>(ca, n, a.b_bf16, a.part + 3 * part_off));
+    int ng = 0;
+    for (int k = 0; k < n;) {
+      int run = 1;  // pairs from k on with the same A and length
+      while (k + run < n && a.A[m0 + k + run] == a.A[m0 + k] && a.numel[m0 + k + run] == a.numel[m0 + k]) ++run;
+      // at least 2048 workgroups (8 per CU) over the run before pairs are grouped:
+      // fewer leave HBM idle, and an A that small is served by the caches anyway
+      const int64_t blocks = cosine_blocks(a.numel[m0 + k]);
+      const int per = (int)std::max<int64_t>(1, std::min<int64_t>(run, run * blocks / 2048));
+      for (int q = 0; q < run; q += per) {
+        ca.A[ng] = a.A[m0 + k];
+        ca.numel[ng] = a.numel[m0 + k];
+        ca.first[ng] = k + q;
+        ca.gblk0[ng++] = nwg;
+        nwg += blocks;
+      }
+      k += run;
+    }
+    ca.first[ng] = n;
+    ca.gblk0[ng] = nwg;
+    if (a.b_bf16)
+      FPO_LAUNCH("cosine", st,
+                 cosine_kernel<true><<<dim3((unsigned)nwg), dim3(256), 0, st>>>(ca, ng, a.part + 3 * part_off));
+    else
+      FPO_LAUNCH("cosine", st,
+                 cosine_kernel<false><<<dim3((unsigned)nwg), dim3(256), 0, st>>>(ca, ng, a.part + 3 * part_off));
     FPO_CHECK_LAUNCH();
     FPO_LAUNCH("cosine_reduce", st,
                cosine_reduce_kernel<<<dim3(n), dim3(256), 0, st>>>(

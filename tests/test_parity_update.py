@@ -177,6 +177,33 @@ def test_clip_edge_cases(dev):
     assert not torch.isnan(W).any()
 
 
+@pytest.mark.parametrize("bdtype", ["f32", "bf16"])
+def test_cosine_shared_signal(dev, bdtype):
+    """Runs of pairs that share A (and its length) are streamed together: groups
+    of several pairs, a last group that is smaller, a ragged last block, a change
+    of A or of length inside the call. Every pair gets the bits of its own call."""
+    g = torch.Generator(device=dev).manual_seed(5)
+    big, small = 1_000_004, 4100  # 245 and 2 blocks a pair: groups of 5 and of 1
+    x, y, z = (torch.randn(m, generator=g, device=dev) for m in (big, big, small))
+    A = [x] * 43 + [y] + [z] * 3 + [x[:small].contiguous()] * 2
+    op = torch.float32 if bdtype == "f32" else torch.bfloat16
+    B = [(a + 0.5 * torch.randn(a.shape, generator=g, device=dev)).to(op) for a in A]
+    n = len(A)
+    out = [torch.empty(n, dtype=torch.float64, device=dev) for _ in range(3)]
+    cs = torch.empty(n, dtype=torch.float32, device=dev)
+    api.fpo_cosine(A, B, dot=out[0], sumsq_A=out[1], sumsq_B=out[2], cos=cs)
+    one = [torch.empty(n, dtype=torch.float64, device=dev) for _ in range(3)]
+    for m in range(n):
+        api.fpo_cosine([A[m]], [B[m]], dot=one[0][m:m + 1], sumsq_A=one[1][m:m + 1], sumsq_B=one[2][m:m + 1])
+    torch.cuda.synchronize()
+    for a, b in zip(out, one):
+        assert torch.equal(a, b)
+    for m in (0, 42, 43, 45, 48):
+        c0 = O.cosine(A[m].cpu().numpy(), I.bf16_bits(B[m].float().cpu().numpy()) if bdtype == "bf16"
+                      else B[m].cpu().numpy())[3]
+        assert abs(float(cs[m]) - c0) <= 1e-6
+
+
 @pytest.mark.parametrize("target", [0, 1], ids=["clip-grad", "clip-update"])
 @pytest.mark.parametrize("kind", [L_.FPO_OPT_SGD, L_.FPO_OPT_ADAMW], ids=["sgd", "adamw"])
 def test_clip_at_zero_weights(dev, kind, target):
