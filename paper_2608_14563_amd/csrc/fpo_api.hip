@@ -255,7 +255,7 @@ size_t carve_pg(const fpo_pg_desc& d, const PgPlan& p, void* ws, fpo::PgLaunch* 
   void* gT = c.take<char>((chain ? d.L : 1) * d.d * p.Tp * esz);
   // norm chain + full-MLP: each layer's signal row-major too (error GEMM operand)
   void* grow = (chain && full) ? c.take<char>(d.L * d.T * d.d * esz) : nullptr;
-  float* pstats = chain ? c.take<float>(4 * d.T) : nullptr;  // per-token norm-chain statistics
+  float* pstats = chain ? c.take<float>(d.L * 4 * d.T) : nullptr;  // per-layer, per-token norm-chain statistics
   void* dq = full ? c.take<char>(d.d_ff * p.Tp * esz) : nullptr;
   void* du = full ? c.take<char>(d.d_ff * p.Tp * esz) : nullptr;
   // tile partials: a region per matrix (3 L with the full MLP: the overlapped

@@ -92,7 +92,7 @@ struct PgLaunch {
   // workspace
   void* gT;                         // [d, Tp] transposed signal
   void* g_row;                      // [T, d] per-layer signal (post-FFN composition, full-MLP)
-  float* chain_stats;               // [T, 4] per-token norm-chain statistics
+  float* chain_stats;               // [L, T, 4] per-token norm-chain statistics
   void* dq_T;                       // [d_ff, Tp] full-MLP gate error (transposed)
   void* du_T;                       // [d_ff, Tp] full-MLP up error (transposed)
   double* part;                     // per-tile partials
