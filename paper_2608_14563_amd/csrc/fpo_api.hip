@@ -74,10 +74,15 @@ struct OePlan {
   int64_t cw = 0, cq = 0;
   int nchunk = 1, nwide = 0;
   int nsplit = 1;
+  int tile = 256;
 };
 
+// Edge of the GEMM tiles by operand type.
+constexpr int kTileBf16 = 256, kTileF32 = 64;
+
+constexpr int64_t kCus = 256;
 // Workgroups one wave of the MI355X grid holds (one 256 x 256 tile per CU).
-constexpr int64_t kWaveSlots = 256;
+constexpr int64_t kWaveSlots = kCus;
 // The staged p~ rows are padded by 256 bytes so that the row pitch is an odd
 // multiple of 256 bytes: with a power-of-two pitch (V = 131072: 256 KiB) the
 // 256 rows of one tile share an L2 set and its stores are written back to HBM
@@ -88,7 +93,9 @@ constexpr int64_t kStageBytes = (int64_t)128 << 20;
 
 OePlan plan_oe(const fpo_oe_desc& d) {
   const bool bf16 = d.dtype == FPO_BF16;
-  const int64_t BM = bf16 ? 256 : 128, BN = BM, WTN = bf16 ? 128 : 64;
+  OePlan p;
+  p.tile = bf16 ? kTileBf16 : kTileF32;
+  const int64_t BM = p.tile, BN = BM, WTN = BN / 2;
   const int64_t pad = kPadBytes / (bf16 ? 2 : 4);
   const int64_t esz = bf16 ? 2 : 4;
   // widest chunk allowed: the caller's width, or by default kStageBytes of
@@ -103,7 +110,6 @@ OePlan plan_oe(const fpo_oe_desc& d) {
     const int64_t lim = std::min(((int64_t)1 << 30) / d.d, ((int64_t)1 << 30) / d.T - pad);
     wmax = std::min(wmax, std::max<int64_t>(256, lim / 256 * 256));
   }
-  OePlan p;
   const int64_t V256 = round_up(d.V, 256);
   if (V256 <= wmax) {
     p.cw = V256;
@@ -146,21 +152,41 @@ OePlan plan_oe(const fpo_oe_desc& d) {
   p.Vc = round_up(widest, 256);
   p.ldp = p.Vc + pad;
   p.nb = p.Vc / WTN;
-  // Split the projection's K range so that its launch fills whole waves: the
-  // smallest split count (at most 8, at least two blocks per split) that gives
-  // at least one wave and the best filled last wave. (T = 4096, d = 3072: 192
-  // tiles, two splits leave the second wave half empty, four fill three.)
   const int64_t tiles = ceil_div(d.T, BM) * ceil_div(d.d, BN);
-  const int64_t nsmax = std::min<int64_t>(8, std::max<int64_t>(1, p.nb / 2));
-  const int64_t ns0 = std::min(nsmax, ceil_div(kWaveSlots, tiles));
-  int64_t best = ns0;
-  double best_fill = 0.0;
-  for (int64_t ns = ns0; ns <= nsmax; ++ns) {
-    const int64_t wg = tiles * ns;
-    const double fill = (double)wg / (double)(ceil_div(wg, kWaveSlots) * kWaveSlots);
-    if (fill > best_fill + 1e-9) {
-      best = ns;
-      best_fill = fill;
+  int64_t best = 1;
+  if (bf16) {
+    // Split the projection's K range so that its launch fills whole waves: the
+    // smallest split count (at most 8, at least two blocks per split) that gives
+    // at least one wave and the best filled last wave. (T = 4096, d = 3072: 192
+    // tiles, two splits leave the second wave half empty, four fill three.)
+    const int64_t nsmax = std::min<int64_t>(8, std::max<int64_t>(1, p.nb / 2));
+    const int64_t ns0 = std::min(nsmax, ceil_div(kWaveSlots, tiles));
+    best = ns0;
+    double best_fill = 0.0;
+    for (int64_t ns = ns0; ns <= nsmax; ++ns) {
+      const int64_t wg = tiles * ns;
+      const double fill = (double)wg / (double)(ceil_div(wg, kWaveSlots) * kWaveSlots);
+      if (fill > best_fill + 1e-9) {
+        best = ns;
+        best_fill = fill;
+      }
+    }
+  } else {
+    // fp32: the split count with the least estimated time. n workgroups share a
+    // CU's matrix pipe (0.47 us per 32-deep K tile, which 1, 2, 3, 4 of them keep
+    // busy 50, 75, 85, 90% of the time); every split adds a partial to write and
+    // to read (5 TB/s) and a load to finalize. Within 3% of the best of 1..32
+    // splits at eight sizes from 128 x 256 x 4096 (T x d x V) to 2048 x 2048 x
+    // 40000; with at most 8 splits and 256 slots, 4 to 12% slower at half of them.
+    static const double kBusy[5] = {0.0, 0.5, 0.75, 0.85, 0.9};
+    double best_us = 0.0;
+    for (int64_t ns = 1; ns <= 32 && 4 * ns <= std::max<int64_t>(4, p.nb); ++ns) {
+      const int64_t n = ceil_div(tiles * ns, kCus), kt = ceil_div(p.nb, ns);
+      const double us = n * kt * 0.47 / kBusy[std::min<int64_t>(n, 4)] + ns * (d.T * d.d * 8 / 5e6 + 0.3);
+      if (best_us == 0.0 || us < best_us) {
+        best = ns;
+        best_us = us;
+      }
     }
   }
   p.nsplit = (int)best;
@@ -232,13 +258,15 @@ int check_oe_desc(const fpo_oe_desc* d) {
 struct PgPlan {
   int64_t Tp = 0, ntiles = 0, upd_blocks = 0;
   int nmats = 0;
+  int tile = 256;
 };
 
 PgPlan plan_pg(const fpo_pg_desc& d) {
   PgPlan p;
   const bool bf16 = d.dtype == FPO_BF16;
   p.Tp = round_up(d.T, 64);
-  p.ntiles = fpo::pseudograd_tiles(bf16, d.d, d.d_ff);
+  p.tile = bf16 ? kTileBf16 : kTileF32;
+  p.ntiles = fpo::pseudograd_tiles(p.tile, d.d, d.d_ff);
   const bool full = (d.mode & FPO_MODE_FULL_MLP) != 0;
   p.nmats = (int)(full ? 3 * d.L : d.L);
   p.upd_blocks = p.nmats * fpo::update_blocks(d.d * d.d_ff);
@@ -470,6 +498,7 @@ int fpo_output_error(const fpo_oe_desc* desc, const void* h_final, const void* g
   L.cq = p.cq;
   L.nwide = p.nwide;
   L.nsplit = p.nsplit;
+  L.tile = p.tile;
   L.eps = desc->eps;
   L.min_rms = desc->min_rms;
   L.h_final = h_final;
@@ -621,6 +650,7 @@ int fpo_pseudograd(const fpo_pg_desc* desc, const void* g_tilde_lp, const void* 
   P.stream = stream;
   const PgPlan pl = plan_pg(*desc);
   P.Tp = pl.Tp;
+  P.tile = pl.tile;
   const size_t need = carve_pg(*desc, pl, nullptr, nullptr, nullptr);
   if (int e = check_ws(ws, ws_bytes, need, "fpo_pseudograd")) return e;
   double* upart = nullptr;

@@ -1,19 +1,28 @@
 // fp32 MFMA tile core for the three contractions of the FPO hot path on
 // gfx950 (the logits Y W_U^T, the projection P W_U and the per-layer outer
 // product g~^T a) when the operands are fp32: one workgroup of 4 waves (2 x 2)
-// computes a 128 x 128 tile of C = A B with v_mfma_f32_16x16x4_f32 (exact
+// computes a 64 x 64 tile of C = A B with v_mfma_f32_16x16x4_f32 (exact
 // fp32 products, fp32 accumulation), A stored K-contiguous ([M][K]
 // row-major) and B either K-contiguous ([N][K], "Bt") or N-contiguous
 // ([K][N]); 32-deep K tiles, register-staged double buffering. bf16 operands
 // run on the LDS-DMA core of gemm2.hpp; TileBF16 here only carries their tile
 // constants.
 //
+// Bound by the matrix pipe (64 flop per cycle and SIMD, 157 TFLOP/s), which
+// waits for nothing else when four workgroups share a CU: a 64 x 64 tile takes
+// 32 KB of LDS and under 128 registers a lane. 128 x 128 tiles (one or two
+// workgroups a CU) were 4 to 25% slower at every size measured with the same
+// loop, and left most of the chip idle at small ones. Eight layers' outer
+// products of 2048 x 2048 x 6144 reach 135 TFLOP/s (127 with the 128 x 128 tiles
+// and operands read right before use), T = 600, d = 1032, V = 20000 logits and
+// projection 88 (73), T = 128, d = 256, V = 4096 13 (6).
+//
 // Lane layout. Within one 32-wide K step every lane l owns the eight K
 // indices 8*(l>>4) + s, s = 0..7, for both operands (the K order inside the
 // sum is a summation order only). Output columns are interleaved: the lane
 // owns columns FN*(l&15) + i, i = 0..FN-1, of its wave's tile, so that its
-// FN accumulator blocks hold FN consecutive output columns (16-byte epilogue
-// stores) and an N-contiguous B tile is read with one 16-byte LDS load per K
+// FN accumulator blocks hold FN consecutive output columns (8-byte epilogue
+// stores) and an N-contiguous B tile is read with one 8-byte LDS load per K
 // row.
 //
 // Accumulator acc[f][i][r] holds C[row, col] with
@@ -34,7 +43,7 @@ struct TileBF16 {
 };
 struct TileF32 {
   using T = float;
-  static constexpr int BM = 128, BN = 128, BK = 32, FM = 4, FN = 4, EPC = 4;
+  static constexpr int BM = 64, BN = 64, BK = 32, FM = 2, FN = 2, EPC = 4;
 };
 
 template <class E>
@@ -48,12 +57,11 @@ struct Tile {
   static constexpr int KC = 8 / EPC;             // chunks per lane per K step
   static constexpr int A_CHUNKS = BM * CPR;
   static constexpr int B_CHUNKS = BN * CPR;      // == BK * BN / EPC
-  static constexpr int BN_CPR = BN / EPC;        // chunks per N-contiguous row (32)
+  static constexpr int BN_CPR = BN / EPC;        // chunks per N-contiguous row
   static constexpr int A_PT = A_CHUNKS / NT;
   static constexpr int BT_PT = B_CHUNKS / NT;
   static constexpr int BNC_PT = (BK * BN_CPR) / NT;
   static_assert(CPR == 8, "swizzle assumes 8 chunks per row");
-  static_assert(BN_CPR == 32, "N-contiguous loader assumes 32 chunks per row");
 };
 
 template <class E>
@@ -65,70 +73,88 @@ struct GemmSmem {
 __device__ __forceinline__ int swz(int row) { return (row ^ (row >> 3)) & 7; }
 
 // ---------------------------------------------------------------- loaders
+// A [M][lda] K-contiguous; B N-contiguous [K][ldb] (BNC) or K-contiguous
+// [N][ldb]. load() takes the K tiles one after the other. Rows (columns) past
+// M (N) take the last one's data: they only reach outputs that no epilogue
+// stores or reduces, so a whole K tile is loaded without any check. In the last,
+// partial K tile whatever lies past K reads as zero.
 template <class E, bool BNC>
 struct TileLoader {
   using TT = Tile<E>;
   using T = typename E::T;
-  u32x4 ra[TT::A_PT];
-  u32x4 rb[BNC ? TT::BNC_PT : TT::BT_PT];
+  static constexpr int NA = TT::A_PT, NB = BNC ? TT::BNC_PT : TT::BT_PT;
+  u32x4 ra[NA], rb[NB];
+  const T* pa[NA];
+  const T* pb[NB];
+  int64_t stepb;
+  int ka, kb[BNC ? NB : 1];  // K index of the lane's chunks (BNC: of its rows) in K tile 0
 
-  // A [M][lda] K-contiguous. Rows >= M and chunks >= K read as zero
-  // (K is a multiple of EPC).
-  __device__ __forceinline__ void load_a(const T* __restrict__ A, int64_t lda, int M, int K, int m0,
-                                         int k0) {
-    const int t = threadIdx.x;
+  __device__ __forceinline__ void setup(const T* __restrict__ A, int64_t lda, int M, int m0,
+                                        const T* __restrict__ B, int64_t ldb, int N, int n0, int kt0) {
+    const int t = threadIdx.x, c = t & 7;
+    const int64_t k0 = (int64_t)kt0 * TT::BK;
+    ka = c * TT::EPC;
 #pragma unroll
-    for (int j = 0; j < TT::A_PT; ++j) {
-      const int row = (t >> 3) + 32 * j, c = t & 7;
-      const int gm = m0 + row, gk = k0 + c * TT::EPC;
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (gm < M && gk < K) v = *reinterpret_cast<const u32x4*>(A + (int64_t)gm * lda + gk);
-      ra[j] = v;
+    for (int j = 0; j < NA; ++j) pa[j] = A + (int64_t)min(m0 + (t >> 3) + 32 * j, M - 1) * lda + k0 + ka;
+    if constexpr (BNC) {
+      const int cc = t % TT::BN_CPR, r = t / TT::BN_CPR;
+      stepb = TT::BK * ldb;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        kb[j] = r + TT::NT / TT::BN_CPR * j;
+        pb[j] = B + (k0 + kb[j]) * ldb + min(n0 + cc * TT::EPC, N - TT::EPC);
+      }
+    } else {
+      stepb = TT::BK;
+      kb[0] = ka;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) pb[j] = B + (int64_t)min(n0 + (t >> 3) + 32 * j, N - 1) * ldb + k0 + ka;
     }
   }
-  __device__ __forceinline__ void store_a(u32x4* sa) {
-    const int t = threadIdx.x;
+  // The loads themselves are unconditional (a branch around them would make the
+  // compiler wait for them where it ends): in the partial K tile chunks past K
+  // read the tile's first ones, and store() writes zeros for them.
+  __device__ __forceinline__ void load(int kt, int K) {
+    const int k_rem = K - kt * TT::BK;
+    if (k_rem < TT::BK) {
 #pragma unroll
-    for (int j = 0; j < TT::A_PT; ++j) {
+      for (int j = 0; j < NA; ++j) pa[j] -= ka < k_rem ? 0 : ka;
+#pragma unroll
+      for (int j = 0; j < NB; ++j) {
+        const int k = kb[BNC ? j : 0];
+        pb[j] -= k < k_rem ? 0 : (BNC ? k * (stepb / TT::BK) : k);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NA; ++j) ra[j] = *reinterpret_cast<const u32x4*>(pa[j]);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) rb[j] = *reinterpret_cast<const u32x4*>(pb[j]);
+#pragma unroll
+    for (int j = 0; j < NA; ++j) pa[j] += TT::BK;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) pb[j] += stepb;
+  }
+  __device__ __forceinline__ void store(u32x4* sa, u32x4* sb, int kt, int K) {
+    const int t = threadIdx.x;
+    const int k_rem = K - kt * TT::BK;
+    if (k_rem < TT::BK) {
+#pragma unroll
+      for (int j = 0; j < NA; ++j)
+        if (ka >= k_rem) ra[j] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        if (kb[BNC ? j : 0] >= k_rem) rb[j] = u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
       const int row = (t >> 3) + 32 * j, c = t & 7;
       sa[row * 8 + (c ^ swz(row))] = ra[j];
     }
-  }
-  // B: N-contiguous [K][ldb] (BNC) or K-contiguous [N][ldb].
-  __device__ __forceinline__ void load_b(const T* __restrict__ B, int64_t ldb, int N, int K, int n0,
-                                         int k0) {
-    const int t = threadIdx.x;
-    if constexpr (BNC) {
 #pragma unroll
-      for (int j = 0; j < TT::BNC_PT; ++j) {
-        const int row = (t >> 5) + 8 * j, c = t & 31;
-        const int gk = k0 + row, gn = n0 + c * TT::EPC;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (gk < K && gn < N) v = *reinterpret_cast<const u32x4*>(B + (int64_t)gk * ldb + gn);
-        rb[j] = v;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < TT::BT_PT; ++j) {
-        const int row = (t >> 3) + 32 * j, c = t & 7;
-        const int gn = n0 + row, gk = k0 + c * TT::EPC;
-        u32x4 v = {0u, 0u, 0u, 0u};
-        if (gn < N && gk < K) v = *reinterpret_cast<const u32x4*>(B + (int64_t)gn * ldb + gk);
-        rb[j] = v;
-      }
-    }
-  }
-  __device__ __forceinline__ void store_b(u32x4* sb) {
-    const int t = threadIdx.x;
-    if constexpr (BNC) {
-#pragma unroll
-      for (int j = 0; j < TT::BNC_PT; ++j) {
-        const int row = (t >> 5) + 8 * j, c = t & 31;
-        sb[row * 32 + c] = rb[j];
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < TT::BT_PT; ++j) {
+    for (int j = 0; j < NB; ++j) {
+      if constexpr (BNC) {
+        sb[t + TT::NT * j] = rb[j];
+      } else {
         const int row = (t >> 3) + 32 * j, c = t & 7;
         sb[row * 8 + (c ^ swz(row))] = rb[j];
       }
@@ -137,103 +163,108 @@ struct TileLoader {
 };
 
 // ---------------------------------------------------------------- compute
-template <bool BNC>
-__device__ __forceinline__ void mma_tile_f32(const u32x4* __restrict__ sa,
-                                             const u32x4* __restrict__ sb,
-                                             f32x4 (&acc)[4][4], int wm, int wn) {
-  using TT = Tile<TileF32>;
+// A wave's operands of one 32-deep K tile, in registers: av[f][s], bv[s][i] for
+// the lane's eight K indices s.
+template <class E>
+struct Frags {
+  f32x4 a[E::FM][2];                                // A fragment f, K indices 4q..4q+3
+  float __attribute__((ext_vector_type(E::FN))) b[8];  // N-contiguous B: columns of K index s
+  f32x4 bt[E::FN][2];                               // K-contiguous B: column i, K indices 4q..4q+3
+};
+
+// The LDS reads of a tile are cut into 8 parts, one issued ahead of the MFMAs
+// of each K index of the tile before it.
+template <class E, bool BNC>
+__device__ __forceinline__ void read_part(Frags<E>& fr, const u32x4* __restrict__ sa,
+                                          const u32x4* __restrict__ sb, int wm, int wn, int part) {
+  using TT = Tile<E>;
+  constexpr int FM = E::FM, FN = E::FN;
+  using fvec = float __attribute__((ext_vector_type(FN)));
   const int l = threadIdx.x & 63;
   const int lr = l & 15, lg = l >> 4;
+  // parts 0 .. FM-1: A fragment `part`, both halves (FM <= 4)
+  if (part < FM) {
+    const int row = wm * TT::WTM + 16 * part + lr;
 #pragma unroll
-  for (int ks = 0; ks < TT::KSTEPS; ++ks) {
-    float av[4][8];
+    for (int q = 0; q < 2; ++q) fr.a[part][q] = __builtin_bit_cast(f32x4, sa[row * 8 + ((2 * lg + q) ^ swz(row))]);
+  }
+  if constexpr (BNC) {  // every part: K index `part`
+    fr.b[part] = reinterpret_cast<const fvec*>(sb)[(8 * lg + part) * (TT::BN / FN) + wn * (TT::WTN / FN) + lr];
+  } else if (part >= 4 && part < 4 + FN) {  // parts 4 ..: column part - 4
+    const int i = part - 4;
+    const int row = wn * TT::WTN + FN * lr + i;
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-      const int row = wm * TT::WTM + 16 * f + lr;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        u32x4 c = sa[row * 8 + ((ks * 8 + 2 * lg + q) ^ swz(row))];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) av[f][4 * q + e] = __uint_as_float(c[e]);
-      }
-    }
-    float bv[8][4];
-    if constexpr (BNC) {
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        const int k = ks * 32 + 8 * lg + s;
-        u32x4 c = sb[k * 32 + wn * (TT::WTN / 4) + lr];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bv[s][i] = __uint_as_float(c[i]);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = wn * TT::WTN + 4 * lr + i;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-          u32x4 c = sb[row * 8 + ((ks * 8 + 2 * lg + q) ^ swz(row))];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) bv[4 * q + e][i] = __uint_as_float(c[e]);
-        }
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < 8; ++s)
-#pragma unroll
-      for (int f = 0; f < 4; ++f)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc[f][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[f][s], bv[s][i], acc[f][i], 0, 0, 0);
+    for (int q = 0; q < 2; ++q) fr.bt[i][q] = __builtin_bit_cast(f32x4, sb[row * 8 + ((2 * lg + q) ^ swz(row))]);
   }
 }
 
+// The MFMAs of K index s.
 template <class E, bool BNC>
-__device__ __forceinline__ void mma_tile(const u32x4* sa, const u32x4* sb,
-                                         f32x4 (&acc)[E::FM][E::FN], int wm, int wn) {
-  static_assert(E::EPC == 4, "this core computes fp32 tiles only");
-  mma_tile_f32<BNC>(sa, sb, acc, wm, wn);
+__device__ __forceinline__ void mma_part(const Frags<E>& fr, f32x4 (&acc)[E::FM][E::FN], int s) {
+#pragma unroll
+  for (int f = 0; f < E::FM; ++f)
+#pragma unroll
+    for (int i = 0; i < E::FN; ++i) {
+      const float bv = BNC ? fr.b[s][i] : fr.bt[i][s >> 2][s & 3];
+      acc[f][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(fr.a[f][s >> 2][s & 3], bv, acc[f][i], 0, 0, 0);
+    }
 }
 
-struct NoHook {
-  template <class Acc>
-  __device__ __forceinline__ void operator()(int, Acc&) const {}
-};
-
-// Main loop over K tiles [kt0, kt1) with LDS double buffering and register
-// prefetch of the next tile. `hook(kt, acc)` runs before tile kt's products
-// are accumulated. Ends with a barrier, so the caller may reuse LDS.
-template <class E, bool BNC, class Hook>
+// Main loop over K tiles [kt0, kt1). While tile kt's products run from
+// registers, tile kt + 1 is read from LDS into a second register set, tile kt + 2
+// goes from its staging registers to the LDS stage that tile kt left, and the
+// loads of tile kt + 3 are issued; everything sits between MFMAs, and one
+// barrier closes the tile. (With each operand read right before its MFMAs and
+// the loads waited for at the end of the tile, the waves that share a SIMD came
+// to meet in the same gaps and the matrix pipe was 60% busy.) Ends with a
+// barrier, so the caller may reuse LDS.
+template <class E, bool BNC>
 __device__ __forceinline__ void gemm_mainloop(GemmSmem<E>& sm, f32x4 (&acc)[E::FM][E::FN],
                                               const typename E::T* __restrict__ A, int64_t lda,
                                               int M, const typename E::T* __restrict__ B,
                                               int64_t ldb, int N, int K, int m0, int n0, int kt0,
-                                              int kt1, const Hook& hook) {
-  using TT = Tile<E>;
+                                              int kt1) {
+  static_assert(E::EPC == 4, "this core computes fp32 tiles only");
   const int w = threadIdx.x >> 6;
   const int wm = w >> 1, wn = w & 1;
   TileLoader<E, BNC> ld;
   if (kt0 >= kt1) return;
-  ld.load_a(A, lda, M, K, m0, kt0 * TT::BK);
-  ld.load_b(B, ldb, N, K, n0, kt0 * TT::BK);
-  ld.store_a(sm.a[0]);
-  ld.store_b(sm.b[0]);
-  __syncthreads();
-  for (int kt = kt0; kt < kt1; ++kt) {
-    const int cur = (kt - kt0) & 1;
-    const bool more = kt + 1 < kt1;
-    if (more) {
-      ld.load_a(A, lda, M, K, m0, (kt + 1) * TT::BK);
-      ld.load_b(B, ldb, N, K, n0, (kt + 1) * TT::BK);
-    }
-    hook(kt, acc);
-    mma_tile<E, BNC>(sm.a[cur], sm.b[cur], acc, wm, wn);
-    if (more) {
-      ld.store_a(sm.a[cur ^ 1]);
-      ld.store_b(sm.b[cur ^ 1]);
-    }
-    __syncthreads();
+  ld.setup(A, lda, M, m0, B, ldb, N, n0, kt0);
+  Frags<E> f0, f1;
+  ld.load(kt0, K);
+  ld.store(sm.a[0], sm.b[0], kt0, K);
+  if (kt0 + 1 < kt1) {
+    ld.load(kt0 + 1, K);
+    ld.store(sm.a[1], sm.b[1], kt0 + 1, K);
   }
+  __syncthreads();
+  if (kt0 + 2 < kt1) ld.load(kt0 + 2, K);
+#pragma unroll
+  for (int p = 0; p < 8; ++p) read_part<E, BNC>(f0, sm.a[0], sm.b[0], wm, wn, p);
+  __syncthreads();
+  // tile kt: operands in cur, its LDS stage st free, tile kt + 1 in stage st ^ 1
+  auto tile = [&](Frags<E>& cur, Frags<E>& nxt, int kt, int st) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) {
+      read_part<E, BNC>(nxt, sm.a[st ^ 1], sm.b[st ^ 1], wm, wn, s);  // past the last tile: unused
+      if (s == 5 && kt + 2 < kt1) ld.store(sm.a[st], sm.b[st], kt + 2, K);
+      if (s == 6 && kt + 3 < kt1) ld.load(kt + 3, K);
+      __builtin_amdgcn_sched_barrier(0);
+      mma_part<E, BNC>(cur, acc, s);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // the LDS writes and reads of this tile; the global loads stay in flight
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  int kt = kt0;
+  for (; kt + 1 < kt1; kt += 2) {
+    tile(f0, f1, kt, 0);
+    tile(f1, f0, kt + 1, 1);
+  }
+  if (kt < kt1) tile(f0, f1, kt, 0);
 }
 
 template <class E>

@@ -100,11 +100,11 @@ constexpr float kRefMargin = 64.f;
 
 __device__ __forceinline__ float block_base(float m, float R) { return m > R + kRefMargin ? m : R; }
 
-// One workgroup: 256 (bf16) / 128 (fp32) tokens x as many vocabulary columns of
-// the chunk; each wave's 128 / 64 columns form one statistics block b (block
+// fp32: one workgroup takes a tile of tokens x vocabulary columns of the chunk;
+// each wave's columns (half the tile's) form one statistics block b (block
 // max m, sum of the staged p~, first arg-max). Columns at or beyond `vc_valid`
 // are masked out; p~ = exp(z - base_b) is staged for the projection.
-template <typename PT, bool CONTIG, class Map, class VA, int FM, int FN>
+template <typename PT, class Map, class VA, int FM, int FN>
 __device__ __forceinline__ void logits_epilogue(VA (&acc)[FM][FN], const Map& mp, int m0,
                                                 int n0, int b, int T, int vc_valid, int v0,
                                                 const float* __restrict__ ref,
@@ -150,15 +150,11 @@ __device__ __forceinline__ void logits_epilogue(VA (&acc)[FM][FN], const Map& mp
       }
       s = wave_sum<Map::LPR>(s);
       if (row < T) {
-        PT* pr = P + (int64_t)row * ldp + n0;
-        if constexpr (CONTIG) {
+        using fvec = float __attribute__((ext_vector_type(FN)));
+        fvec v;
 #pragma unroll
-          for (int i = 0; i < FN; i += 4)
-            st4(pr, mp.col(i), f32x4{p[i], p[i + 1], p[i + 2], p[i + 3]});
-        } else {
-#pragma unroll
-          for (int i = 0; i < FN; ++i) st_from_f32(pr, mp.col(i), p[i]);
-        }
+        for (int i = 0; i < FN; ++i) v[i] = p[i];
+        *reinterpret_cast<fvec*>(P + (int64_t)row * ldp + n0 + mp.col(0)) = v;  // FN consecutive columns
         if (lr == 0 && b < nb) {
           const int64_t o = (int64_t)row * nb + b;
           blk_m[o] = m;
@@ -306,8 +302,8 @@ __global__ __launch_bounds__(256, 1) void logits_chunk_kernel(
     zero_acc<E>(acc);
     const int b = n0 / TT::WTN + ((threadIdx.x >> 6) & 1);  // this wave's block
     gemm_mainloop<E, false>(sm, acc, y, d, T, Wc, d, vc_valid, d, m0, n0, 0,
-                            (d + TT::BK - 1) / TT::BK, NoHook{});
-    logits_epilogue<typename E::T, true>(acc, AccMap<E>(), m0, n0, b, T, vc_valid, v0, ref, P, ldp, nb,
+                            (d + TT::BK - 1) / TT::BK);
+    logits_epilogue<typename E::T>(acc, AccMap<E>(), m0, n0, b, T, vc_valid, v0, ref, P, ldp, nb,
                                          blk_m, blk_s, blk_i);
   }
 }
@@ -329,7 +325,7 @@ __global__ __launch_bounds__(256) void chunk_stats_kernel(
     int T, int nb, int first, const float* __restrict__ blk_m, const float* __restrict__ blk_s,
     const int32_t* __restrict__ blk_i, float* __restrict__ ref, float* __restrict__ runM,
     float* __restrict__ runS, int32_t* __restrict__ runA, float* __restrict__ fout,
-    float* __restrict__ alpha, PT* __restrict__ P, int64_t ldp) {
+    float* __restrict__ alpha, PT* __restrict__ P, int64_t ldp, int blkw) {
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + w;
   if (row >= T) return;  // whole wave exits together; no barrier below
@@ -385,11 +381,11 @@ __global__ __launch_bounds__(256) void chunk_stats_kernel(
   // a block above R + kRefMargin makes the chunk maximum exceed every base_b
   const float Ref = any_own ? mc : R;
   if (any_own) {
-    // the token's staged row, 16-byte runs; 16 runs per block for both
-    // element types (128 bf16 or 64 fp32 entries)
+    // the token's staged row, 16-byte runs
     u32x4* pr = reinterpret_cast<u32x4*>(P + (int64_t)row * ldp);
-    for (int c = l; c < nb * 16; c += 64) {
-      const float bb = block_base(bm[c >> 4], R);
+    const int runs = blkw * (int)sizeof(PT) / 16;  // per block
+    for (int c = l; c < nb * runs; c += 64) {
+      const float bb = block_base(bm[c / runs], R);
       if (bb == Ref) continue;
       const float f = __expf(bb - Ref);
       u32x4 v = pr[c];
@@ -433,14 +429,13 @@ __device__ __forceinline__ void proj_epilogue(VA (&acc)[FM][FN], const Map& mp, 
       if (row >= T || c >= d) continue;
       const float so = fout[row];
       const float sa = first ? 0.f : alpha[row];
+      using fvec = float __attribute__((ext_vector_type(FN)));
+      fvec* gp = reinterpret_cast<fvec*>(Gs + (int64_t)row * d + c);
+      fvec o;
 #pragma unroll
-      for (int i = 0; i < FN; i += 4) {
-        float* gp = Gs + (int64_t)row * d + c + i;
-        f32x4 o = {acc[f][i][r] * so, acc[f][i + 1][r] * so, acc[f][i + 2][r] * so,
-                   acc[f][i + 3][r] * so};
-        if (!first) o += *reinterpret_cast<const f32x4*>(gp) * sa;
-        *reinterpret_cast<f32x4*>(gp) = o;
-      }
+      for (int i = 0; i < FN; ++i) o[i] = acc[f][i][r] * so;
+      if (!first) o += *gp * sa;
+      *gp = o;
     }
 }
 
@@ -516,7 +511,7 @@ __global__ __launch_bounds__(256, 1) void proj_chunk_kernel(
     const int tpb = blkw / TT::BK;
     const int nkt = (vc_valid + TT::BK - 1) / TT::BK;
     const int kt0 = min(sp * bps * tpb, nkt), kt1 = min(min(nb, (sp + 1) * bps) * tpb, nkt);
-    gemm_mainloop<E, true>(sm, acc, P, ldp, T, Wc, d, d, vc_valid, m0, n0, kt0, kt1, NoHook{});
+    gemm_mainloop<E, true>(sm, acc, P, ldp, T, Wc, d, d, vc_valid, m0, n0, kt0, kt1);
     proj_epilogue(acc, AccMap<E>(), m0, n0, T, d, first, fout, alpha, Gs);
   }
 }
@@ -654,7 +649,7 @@ static hipError_t run_output_error(const OeLaunch& a) {
     FPO_LAUNCH("chunk_stats", st,
                chunk_stats_kernel<T><<<dim3((unsigned)((a.T + 3) / 4)), dim3(256), 0, st>>>(
         (int)a.T, nbv, c == 0, a.blk_m, a.blk_s, a.blk_i, a.ref, a.runM, a.runS, a.runA, a.fout, a.alpha,
-        P, a.ldp));
+        P, a.ldp, TT::WTN));
     FPO_CHECK_LAUNCH();
     const int bps = (nbv + a.nsplit - 1) / a.nsplit;
     const bool fast_p = a.T % TT::BM == 0 && a.d % TT::BN == 0 && vc_valid % 64 == 0;

@@ -182,17 +182,21 @@ __device__ __forceinline__ void outer_epilogue(VA (&acc)[FM][FN], const Map& mp,
       const int row = m0 + mp.row(f, r);
       const int c = n0 + mp.col(0);  // FN consecutive columns
       if (row >= M || c >= N) continue;  // N % 8 == 0: a lane's columns are all in or all out
+      using fvec = float __attribute__((ext_vector_type(FN)));
+      const int64_t o = (int64_t)row * N + c;
+      fvec v;
 #pragma unroll
-      for (int i = 0; i < FN; i += 4) {
-        f32x4 v = {acc[f][i][r] * scale, acc[f][i + 1][r] * scale, acc[f][i + 2][r] * scale,
-                   acc[f][i + 3][r] * scale};
-        const int64_t o = (int64_t)row * N + c + i;
-        if (C) *reinterpret_cast<f32x4*>(C + o) = v;
-        ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-        if (R) {
-          f32x4 q = *reinterpret_cast<const f32x4*>(R + o);
-          dt += v.x * q.x + v.y * q.y + v.z * q.z + v.w * q.w;
-          rr += q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
+      for (int i = 0; i < FN; ++i) {
+        v[i] = acc[f][i][r] * scale;
+        ss += v[i] * v[i];
+      }
+      if (C) *reinterpret_cast<fvec*>(C + o) = v;
+      if (R) {
+        const fvec q = *reinterpret_cast<const fvec*>(R + o);
+#pragma unroll
+        for (int i = 0; i < FN; ++i) {
+          dt += v[i] * q[i];
+          rr += q[i] * q[i];
         }
       }
     }
@@ -301,8 +305,7 @@ __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, in
     __shared__ GemmSmem<E> sm;
     f32x4 acc[E::FM][E::FN];
     zero_acc<E>(acc);
-    gemm_mainloop<E, true>(sm, acc, Am, lda, M, Bm, ldb, N, K, m0, n0, 0, (K + TT::BK - 1) / TT::BK,
-                           NoHook{});
+    gemm_mainloop<E, true>(sm, acc, Am, lda, M, Bm, ldb, N, K, m0, n0, 0, (K + TT::BK - 1) / TT::BK);
     outer_epilogue(acc, AccMap<E>(), m0, n0, M, N, scale, args.C[mat], args.R[mat], red, po);
   }
 }
@@ -505,7 +508,7 @@ __global__ __launch_bounds__(256, 1) void errh_kernel(const typename E::T* __res
     f32x4 acc[E::FM][E::FN];
     zero_acc<E>(acc);
     gemm_mainloop<E, true>(sm, acc, g, d, T, W3i, d_ff, d_ff, d, m0, n0, 0,
-                           (d + TT::BK - 1) / TT::BK, NoHook{});
+                           (d + TT::BK - 1) / TT::BK);
     errh_epilogue<typename E::T>(acc, AccMap<E>(), m0, n0, q, u, T, Tp, d_ff, dq_T, du_T);
   }
 }
@@ -539,9 +542,8 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const double* __restr
   }
 }
 
-int64_t pseudograd_tiles(bool bf16, int64_t M, int64_t N) {
-  const int BM = bf16 ? TileBF16::BM : TileF32::BM, BN = bf16 ? TileBF16::BN : TileF32::BN;
-  return ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
+int64_t pseudograd_tiles(int tile, int64_t M, int64_t N) {
+  return ((M + tile - 1) / tile) * ((N + tile - 1) / tile);
 }
 
 #define FPO_CHECK_LAUNCH()             \
@@ -631,8 +633,8 @@ static hipError_t run_pseudograd(const PgLaunch& a) {
   using T = typename E::T;
   using TT = Tile<E>;
   hipStream_t st = (hipStream_t)a.stream;
-  const int ntiles = (int)pseudograd_tiles(a.bf16, a.d, a.d_ff);
-  const int ntiles2 = (int)pseudograd_tiles(a.bf16, a.d_ff, a.d);
+  const int ntiles = (int)pseudograd_tiles(a.tile, a.d, a.d_ff);
+  const int ntiles2 = (int)pseudograd_tiles(a.tile, a.d_ff, a.d);
   hipError_t e;
   if ((e = prepare_signals<T>(a, st)) != hipSuccess) return e;
   // W3 outer products of every layer (M = d, N = d_ff, K = T) in one launch
@@ -752,8 +754,8 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
   hipStream_t st = (hipStream_t)a.stream;
   hipError_t e;
   if ((e = prepare_signals<uint16_t>(a, st)) != hipSuccess) return e;
-  const int ntiles = (int)pseudograd_tiles(true, a.d, a.d_ff);
-  const int ntiles2 = (int)pseudograd_tiles(true, a.d_ff, a.d);
+  const int ntiles = (int)pseudograd_tiles(a.tile, a.d, a.d_ff);
+  const int ntiles2 = (int)pseudograd_tiles(a.tile, a.d_ff, a.d);
   // matrix m: W3 of layer m (m < L), then W1 and W2 of layer l at L + l and
   // 2 L + l; its update blocks start at the sum of the earlier matrices'
   // blocks. Tile partials have a region per matrix (the side stream reads them

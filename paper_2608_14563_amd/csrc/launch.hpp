@@ -27,6 +27,7 @@ struct OeLaunch {
   int nchunk, nwide;    // chunk layout (chunk_span)
   int64_t cw, cq;
   int nsplit;
+  int tile;             // edge of the GEMM tiles: 256 (bf16) or 64 (fp32)
   float eps, min_rms;
   const void* h_final;
   const void* gamma;
@@ -62,6 +63,7 @@ struct PgLaunch {
   bool full_mlp;
   int64_t T, d, d_ff, Tp;
   int L;
+  int tile;                         // edge of the GEMM tiles, as in OeLaunch
   float scale;
   const void* g_lp;                 // [T, d]
   const void* a[kMaxMats];          // [T, d_ff]
@@ -99,7 +101,7 @@ struct PgLaunch {
   void* stream;
 };
 hipError_t launch_pseudograd(const PgLaunch& a);
-int64_t pseudograd_tiles(bool bf16, int64_t M, int64_t N);
+int64_t pseudograd_tiles(int tile, int64_t M, int64_t N);
 
 constexpr int kOptAdamW = 1;  // fpo_opt_kind FPO_OPT_ADAMW
 

@@ -80,6 +80,16 @@ def test_bf16_ragged(dev, T, d, V, chunk):
     check_against_oracle(x, g, W, y, "bf16", got)
 
 
+@pytest.mark.parametrize("T,d,V", [(64, 32, 64), (65, 40, 72), (63, 64, 136), (1, 72, 4096), (128, 96, 200),
+                                   (129, 104, 3000), (20, 8, 33000)])
+def test_fp32_tile_edges(dev, T, d, V):
+    """One to four 32-deep K tiles with a whole or a partial last one, a row or
+    column more or less than a 64 x 64 tile, up to 32 projection splits."""
+    c, x, g, W, y = small_case(I.CONFIGS[0], T, d, V)
+    got = run_gpu(x, g, W, y, "f32", dev)
+    check_against_oracle(x, g, W, y, "f32", got)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_more_tokens_than_a_second_grid_dimension_holds(dev, dtype):
     """T = 65600, above the 65536 cap of a second grid dimension: the
