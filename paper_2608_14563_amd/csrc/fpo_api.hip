@@ -37,7 +37,8 @@ int hip_fail(hipError_t e, const char* where) {
   return fail(FPO_ERR_HIP, "%s: %s (%d)", where, hipGetErrorString(e), (int)e);
 }
 
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+using fpo::ceil_div;
+using fpo::kCus;
 inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 inline bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
@@ -80,7 +81,6 @@ struct OePlan {
 // Edge of the GEMM tiles by operand type.
 constexpr int kTileBf16 = 256, kTileF32 = 64;
 
-constexpr int64_t kCus = 256;
 // Workgroups one wave of the MI355X grid holds (one 256 x 256 tile per CU).
 constexpr int64_t kWaveSlots = kCus;
 // The staged p~ rows are padded by 256 bytes so that the row pitch is an odd
@@ -95,7 +95,7 @@ OePlan plan_oe(const fpo_oe_desc& d) {
   const bool bf16 = d.dtype == FPO_BF16;
   OePlan p;
   p.tile = bf16 ? kTileBf16 : kTileF32;
-  const int64_t BM = p.tile, BN = BM, WTN = BN / 2;
+  const int64_t BM = p.tile, BN = BM, SB = BN / 2;  // SB: statistics block
   const int64_t pad = kPadBytes / (bf16 ? 2 : 4);
   const int64_t esz = bf16 ? 2 : 4;
   // widest chunk allowed: the caller's width, or by default kStageBytes of
@@ -151,24 +151,18 @@ OePlan plan_oe(const fpo_oe_desc& d) {
   }
   p.Vc = round_up(widest, 256);
   p.ldp = p.Vc + pad;
-  p.nb = p.Vc / WTN;
-  const int64_t tiles = ceil_div(d.T, BM) * ceil_div(d.d, BN);
+  p.nb = p.Vc / SB;
   int64_t best = 1;
   if (bf16) {
-    // Split the projection's K range so that its launch fills whole waves: the
-    // smallest split count (at most 8, at least two blocks per split) that gives
-    // at least one wave and the best filled last wave. (T = 4096, d = 3072: 192
-    // tiles, two splits leave the second wave half empty, four fill three.)
-    const int64_t nsmax = std::min<int64_t>(8, std::max<int64_t>(1, p.nb / 2));
-    const int64_t ns0 = std::min(nsmax, ceil_div(kWaveSlots, tiles));
-    best = ns0;
-    double best_fill = 0.0;
-    for (int64_t ns = ns0; ns <= nsmax; ++ns) {
-      const int64_t wg = tiles * ns;
-      const double fill = (double)wg / (double)(ceil_div(wg, kWaveSlots) * kWaveSlots);
-      if (fill > best_fill + 1e-9) {
+    // The split count with the least estimated time (big_tiles); every split adds
+    // a partial to write and to read (5 TB/s) and a load to finalize.
+    double best_us = 0.0;
+    for (int64_t ns = 1; ns <= 32 && ns <= std::max<int64_t>(1, p.nb / 2); ++ns) {
+      const double us = fpo::big_tiles(d.T, d.d, ceil_div(p.nb, ns) * SB, ns, d.d).us +
+                        ns * (d.T * d.d * 8 / 5e6 + 0.3);
+      if (best_us == 0.0 || us < best_us) {
         best = ns;
-        best_fill = fill;
+        best_us = us;
       }
     }
   } else {
@@ -179,6 +173,7 @@ OePlan plan_oe(const fpo_oe_desc& d) {
     // splits at eight sizes from 128 x 256 x 4096 (T x d x V) to 2048 x 2048 x
     // 40000; with at most 8 splits and 256 slots, 4 to 12% slower at half of them.
     static const double kBusy[5] = {0.0, 0.5, 0.75, 0.85, 0.9};
+    const int64_t tiles = ceil_div(d.T, BM) * ceil_div(d.d, BN);
     double best_us = 0.0;
     for (int64_t ns = 1; ns <= 32 && 4 * ns <= std::max<int64_t>(4, p.nb); ++ns) {
       const int64_t n = ceil_div(tiles * ns, kCus), kt = ceil_div(p.nb, ns);
@@ -286,9 +281,9 @@ size_t carve_pg(const fpo_pg_desc& d, const PgPlan& p, void* ws, fpo::PgLaunch* 
   float* pstats = chain ? c.take<float>(d.L * 4 * d.T) : nullptr;  // per-layer, per-token norm-chain statistics
   void* dq = full ? c.take<char>(d.d_ff * p.Tp * esz) : nullptr;
   void* du = full ? c.take<char>(d.d_ff * p.Tp * esz) : nullptr;
-  // tile partials: a region per matrix (3 L with the full MLP: the overlapped
+  // tile partials (up to four per tile): a region per matrix (3 L with the full MLP: the overlapped
   // update reduces each matrix's partials while later launches run)
-  double* part = c.take<double>((full ? 3 * d.L : std::max<int64_t>(d.L, 2)) * p.ntiles * 3);
+  double* part = c.take<double>((full ? 3 * d.L : std::max<int64_t>(d.L, 2)) * 4 * p.ntiles * 3);
   double* up = c.take<double>(p.upd_blocks);
   double* dsq = c.take<double>(p.nmats);  // ||delta||^2 per matrix (clip-the-update mode)
   // staged bf16 pseudogradients (FPO_MODE_GRAD_BF16), one 256-aligned matrix per layer
@@ -498,7 +493,6 @@ int fpo_output_error(const fpo_oe_desc* desc, const void* h_final, const void* g
   L.cq = p.cq;
   L.nwide = p.nwide;
   L.nsplit = p.nsplit;
-  L.tile = p.tile;
   L.eps = desc->eps;
   L.min_rms = desc->min_rms;
   L.h_final = h_final;

@@ -37,19 +37,24 @@
 
 namespace fpo {
 
-struct TileBF16 {
+// SB: width of a logits statistics block (the columns of one wave).
+struct TileBF16 {  // gemm2.hpp
   using T = uint16_t;
-  static constexpr int BM = 256, BN = 256, BK = 64, FM = 8, FN = 8, EPC = 8;
+  static constexpr int BM = 256, BN = 256, BK = 64, FM = 8, FN = 8, EPC = 8, SB = 128;
+};
+struct TileBF16S {  // gemm2s.hpp
+  using T = uint16_t;
+  static constexpr int BM = 128, BN = 128, BK = 64, FM = 4, FN = 4, EPC = 8, SB = 128;
 };
 struct TileF32 {
   using T = float;
-  static constexpr int BM = 64, BN = 64, BK = 32, FM = 2, FN = 2, EPC = 4;
+  static constexpr int BM = 64, BN = 64, BK = 32, FM = 2, FN = 2, EPC = 4, SB = 32;
 };
 
 template <class E>
 struct Tile {
   using T = typename E::T;
-  static constexpr int BM = E::BM, BN = E::BN, BK = E::BK, FM = E::FM, FN = E::FN, EPC = E::EPC;
+  static constexpr int BM = E::BM, BN = E::BN, BK = E::BK, FM = E::FM, FN = E::FN, EPC = E::EPC, SB = E::SB;
   static constexpr int NT = 256;                 // threads per workgroup
   static constexpr int WTM = 16 * FM, WTN = 16 * FN;
   static constexpr int CPR = BK / EPC;           // chunks per K-contiguous row (8)
@@ -296,6 +301,30 @@ __device__ __forceinline__ void grouped_tile(int id, int ntm, int ntn, int gm, i
   const int r = id % width;
   tm = first + r % rows;
   tn = r / rows;
+}
+
+// A uniform value that the compiler may have computed in vector registers (an
+// integer division), in a scalar one: the copies' scalar offsets derive from it.
+// Not the builtin, which is folded away where the value is known to be uniform.
+__device__ __forceinline__ int to_scalar(int v) {
+  int s;
+  asm("v_readfirstlane_b32 %0, %1" : "=s"(s) : "v"(v));
+  return s;
+}
+
+// Tile of a workgroup: ids [0, nbig) are tiles of the 256 x 256 grid (tm, tn),
+// in a launch of their own; the grid's other tiles are taken as four 128 x 128
+// quarters each by a second launch, in whose units (tm, tn) then are (a quarter
+// may lie outside a ragged matrix).
+template <bool QUARTERS>
+__device__ __forceinline__ void split_tile(int id, int nbig, int ntm, int ntn, int& tm, int& tn) {
+  if constexpr (QUARTERS) {
+    grouped_tile(nbig + (id >> 2), ntm, ntn, 8, tm, tn);
+    tm = 2 * tm + (id & 1);
+    tn = 2 * tn + ((id >> 1) & 1);
+  } else {
+    grouped_tile(id, ntm, ntn, 8, tm, tn);
+  }
 }
 
 // Output coordinates of accumulator element [f][i][r] (relative to the tile).

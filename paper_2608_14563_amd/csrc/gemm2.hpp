@@ -416,11 +416,20 @@ __device__ __forceinline__ void zero_acc2(f32x16 (&acc)[4][4]) {
     for (int i = 0; i < 4; ++i) acc[f][i] = f32x16{};
 }
 
+// VEC consecutive columns of one row, from accumulators i .. i + VEC - 1.
+template <int VEC> struct FVec;
+template <> struct FVec<4> { using T = f32x4; };
+template <> struct FVec<1> { using T = float; };
+template <int VEC, int FN>
+__device__ __forceinline__ typename FVec<VEC>::T acc_vec(const f32x16 (&a)[FN], int i, int r) {
+  if constexpr (VEC == 4) return f32x4{a[i][r], a[i + 1][r], a[i + 2][r], a[i + 3][r]};
+  else return a[i][r];
+}
+
 // Output coordinates of acc[f][i] element r relative to the tile.
 template <bool BNC>
 struct AccMap2 {
-  static constexpr int R = 16;    // accumulator elements per (f, i): 4 groups of 4 consecutive rows
-  static constexpr int LPR = 32;  // lanes sharing one output row
+  static constexpr int VEC = BNC ? 4 : 1;  // consecutive columns of a lane
   int row0, colb, lc;
   __device__ __forceinline__ AccMap2() {
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;

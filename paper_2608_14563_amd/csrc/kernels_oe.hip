@@ -14,8 +14,11 @@
 // is staged between the logits and projection launches of that chunk.
 #include "gemm.hpp"
 #include "gemm2.hpp"
+#include "gemm2s.hpp"
 #include "launch.hpp"
 #include "prof.hpp"
+
+#include <type_traits>
 
 namespace fpo {
 
@@ -177,29 +180,34 @@ __device__ __forceinline__ void logits_epilogue(VA (&acc)[FM][FN], const Map& mp
 // c ^ (r & 31) (the 32 token rows of one 8-byte write, and the 32 chunks of
 // one row read back, fall in distinct 16-byte slots), then written out as
 // whole 512-byte token rows: scattered 8-byte runs cost 7% of the kernel.
-template <bool RAGGED>
-__device__ __forceinline__ void logits_epilogue_vt(const f32x16 (&acc)[4][4], G2Smem& sm, int vt0,
-                                                   int tt0, int T, int vc_valid, int v0,
+//
+// wm, wn: the wave's vocabulary block and its group of 32 FN tokens in the tile
+// of VT entries x NT tokens; with 128-entry tiles a token row is 256 bytes, 16
+// chunks, swizzled by r & 15.
+template <bool RAGGED, int VT, int NT, int FN>
+__device__ __forceinline__ void logits_epilogue_vt(const f32x16 (&acc)[4][FN], u32x4* __restrict__ lds, int wm,
+                                                   int wn, int vt0, int tt0, int T, int vc_valid, int v0,
                                                    const float* __restrict__ ref,
                                                    uint16_t* __restrict__ P, int64_t ldp, int nb,
                                                    float* __restrict__ blk_m,
                                                    float* __restrict__ blk_s,
                                                    int32_t* __restrict__ blk_i) {
-  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  constexpr int kChunks = VT / 8;  // 16-byte chunks per staged token row
+  const int l = threadIdx.x & 63;
   const int lc = l & 31, h = l >> 5;
-  const int vw = vt0 + (w >> 1) * G2::WTM;  // chunk-relative first entry of the wave's block
-  const int b = vw / G2::WTM;
+  const int vw = vt0 + wm * 128;   // chunk-relative first entry of the wave's block
+  const int b = vw / 128;
   const int vl = vw + 4 * h;                // entry of offset 0 in this lane
   const int lim = vc_valid - vl;            // offset o is in range iff o < lim (RAGGED only)
-  float R[4];
+  float R[FN];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int t = tt0 + (w & 1) * G2::WTN + 32 * i + lc;
+  for (int i = 0; i < FN; ++i) {
+    const int t = tt0 + 32 * (wn * FN + i) + lc;
     R[i] = t < T ? ref[t] : 0.f;
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int t = tt0 + (w & 1) * G2::WTN + 32 * i + lc;
+  for (int i = 0; i < FN; ++i) {
+    const int t = tt0 + 32 * (wn * FN + i) + lc;
     // block maximum, then its first (lowest) entry; offsets o = 32f + 8q + j
     // increase with (f, r)
     float m = -INFINITY;
@@ -233,9 +241,9 @@ __device__ __forceinline__ void logits_epilogue_vt(const f32x16 (&acc)[4][4], G2
     const float nb2 = -base * 1.44269504088896341f;
     float s = 0.f;
     // LDS token row of this lane and the tile column of its entries at f = q = 0
-    const int lrow = (w & 1) * G2::WTN + 32 * i + lc;
+    const int lrow = 32 * (wn * FN + i) + lc;
     const int col0 = vl - vt0;
-    char* lds_row = reinterpret_cast<char*>(sm.s) + lrow * 512 + (col0 & 7) * 2;
+    char* lds_row = reinterpret_cast<char*>(lds) + lrow * (VT * 2) + (col0 & 7) * 2;
 #pragma unroll
     for (int f = 0; f < 4; ++f)
 #pragma unroll
@@ -248,7 +256,7 @@ __device__ __forceinline__ void logits_epilogue_vt(const f32x16 (&acc)[4][4], G2
                                       : 0.f;
           s += p[j];
         }
-        const int chunk = ((col0 + 32 * f + 8 * q) >> 3) ^ lc;  // lrow & 31 == lc
+        const int chunk = ((col0 + 32 * f + 8 * q) >> 3) ^ (lc & (kChunks - 1));  // lrow & 31 == lc
         *reinterpret_cast<u32x2*>(lds_row + chunk * 16) = u32x2{pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3])};
       }
     s += __shfl_xor(s, 32, 64);
@@ -260,16 +268,15 @@ __device__ __forceinline__ void logits_epilogue_vt(const f32x16 (&acc)[4][4], G2
     }
   }
   __syncthreads();
-  // whole token rows out: each half-wave one row, 16 bytes per lane (entries
-  // past vc_valid were staged as zeros; the tile lies inside the chunk's Vc
-  // columns)
-  const int c = threadIdx.x & 31;
+  // whole token rows out, 16 bytes per lane (entries past vc_valid were staged
+  // as zeros; the tile lies inside the chunk's Vc columns)
+  const int c = threadIdx.x & (kChunks - 1);
 #pragma unroll 4
-  for (int k = 0; k < 32; ++k) {
-    const int r = (int)(threadIdx.x >> 5) + 8 * k;
+  for (int k = 0; k < NT * kChunks / 256; ++k) {
+    const int r = (int)threadIdx.x / kChunks + 256 / kChunks * k;
     const int t = tt0 + r;
     if (t >= T) break;  // rows increase with k
-    const u32x4 v = sm.s[r * 32 + (c ^ (r & 31))];
+    const u32x4 v = lds[r * kChunks + (c ^ (r & (kChunks - 1)))];
     *reinterpret_cast<u32x4*>(P + (int64_t)t * ldp + vt0 + 8 * c) = v;
   }
 }
@@ -278,14 +285,30 @@ template <class E, bool FAST>
 __global__ __launch_bounds__(256, 1) void logits_chunk_kernel(
     const typename E::T* __restrict__ y, const typename E::T* __restrict__ Wc, int T, int d,
     int vc_valid, int v0, const float* __restrict__ ref, typename E::T* __restrict__ P, int64_t ldp,
-    int nb, float* __restrict__ blk_m, float* __restrict__ blk_s, int32_t* __restrict__ blk_i) {
+    int nb, float* __restrict__ blk_m, float* __restrict__ blk_s, int32_t* __restrict__ blk_i, int nbig) {
   using TT = Tile<E>;
-  const int ntm = (T + TT::BM - 1) / TT::BM, ntn = (vc_valid + TT::BN - 1) / TT::BN;
+  constexpr bool kQuarters = E::EPC == 8 && E::BM == 128;
+  constexpr int kEdge = kQuarters ? 256 : TT::BM;
+  const int ntm = (T + kEdge - 1) / kEdge, ntn = (vc_valid + kEdge - 1) / kEdge;
   int tm, tn;
   // consecutive workgroups share a vocabulary band and sweep the token tiles
-  grouped_tile(xcd_remap(blockIdx.x, gridDim.x), ntm, ntn, 8, tm, tn);
+  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn, tm, tn);
   const int m0 = tm * TT::BM, n0 = tn * TT::BN;
-  if constexpr (E::EPC == 8) {
+  if constexpr (kQuarters) {
+    if (m0 >= T || n0 >= vc_valid) return;
+    __shared__ G2SSmem sm;
+    f32x16 acc[4][1];
+    zero_acc2s<false>(acc);
+    const Operand A{Wc + (int64_t)n0 * d, d, band_bytes(vc_valid - n0, d)};
+    const Operand B{y + (int64_t)m0 * d, d, band_bytes(T - m0, d)};
+    gemm2s_mainloop<false>(sm, acc, A, B, vc_valid - n0, T - m0, d, 0, (d + G2S::BK - 1) / G2S::BK);
+    if (n0 + 128 <= vc_valid)
+      logits_epilogue_vt<false, 128, 128, 1>(acc, sm.s, 0, threadIdx.x >> 6, n0, m0, T, vc_valid, v0, ref, P, ldp, nb,
+                                             blk_m, blk_s, blk_i);
+    else
+      logits_epilogue_vt<true, 128, 128, 1>(acc, sm.s, 0, threadIdx.x >> 6, n0, m0, T, vc_valid, v0, ref, P, ldp, nb,
+                                            blk_m, blk_s, blk_i);
+  } else if constexpr (E::EPC == 8) {
     __shared__ G2Smem sm;
     f32x16 acc[4][4];
     zero_acc2(acc);
@@ -293,9 +316,11 @@ __global__ __launch_bounds__(256, 1) void logits_chunk_kernel(
     const Operand B{y + (int64_t)m0 * d, d, band_bytes(T - m0, d)};
     gemm2_mainloop<false, FAST>(sm, acc, A, B, vc_valid - n0, T - m0, d, 0, (d + G2::BK - 1) / G2::BK);
     if (FAST || n0 + ((threadIdx.x >> 7) + 1) * G2::WTM <= vc_valid)  // wave-uniform; FAST: whole tiles
-      logits_epilogue_vt<false>(acc, sm, n0, m0, T, vc_valid, v0, ref, P, ldp, nb, blk_m, blk_s, blk_i);
+      logits_epilogue_vt<false, 256, 256, 4>(acc, sm.s, threadIdx.x >> 7, (threadIdx.x >> 6) & 1, n0, m0, T,
+                                             vc_valid, v0, ref, P, ldp, nb, blk_m, blk_s, blk_i);
     else
-      logits_epilogue_vt<true>(acc, sm, n0, m0, T, vc_valid, v0, ref, P, ldp, nb, blk_m, blk_s, blk_i);
+      logits_epilogue_vt<true, 256, 256, 4>(acc, sm.s, threadIdx.x >> 7, (threadIdx.x >> 6) & 1, n0, m0, T, vc_valid,
+                                            v0, ref, P, ldp, nb, blk_m, blk_s, blk_i);
   } else {
     __shared__ GemmSmem<E> sm;
     f32x4 acc[E::FM][E::FN];
@@ -443,40 +468,47 @@ __device__ __forceinline__ void proj_epilogue(VA (&acc)[FM][FN], const Map& mp, 
 // exp(M_old - M_new) are staged in LDS (the ring is free after the main loop)
 // and each fragment's 16 partial rows are loaded together before use, so the
 // row loads overlap instead of serialising on their latency.
-__device__ __forceinline__ void proj_epilogue2(f32x16 (&acc)[4][4], G2Smem& sm, int m0, int n0,
-                                               int T, int d, int first,
+template <int BM, class Map, int FM, int FN>
+__device__ __forceinline__ void proj_epilogue2(f32x16 (&acc)[FM][FN], const Map& mp, float* __restrict__ sf, int m0,
+                                               int n0, int T, int d, int first,
                                                const float* __restrict__ fout,
                                                const float* __restrict__ alpha,
                                                float* __restrict__ Gs) {
-  float* sf = reinterpret_cast<float*>(sm.s);
-  {
+  constexpr int VEC = Map::VEC;
+  using fvec = typename FVec<VEC>::T;
+  if (threadIdx.x < BM) {
     const int rr = m0 + (int)threadIdx.x;
     sf[threadIdx.x] = rr < T ? fout[rr] : 0.f;
-    sf[256 + threadIdx.x] = (!first && rr < T) ? alpha[rr] : 0.f;
+    sf[BM + threadIdx.x] = (!first && rr < T) ? alpha[rr] : 0.f;
   }
   __syncthreads();
-  const AccMap2<true> mp;
-  const int c = n0 + mp.col(0);  // 4 consecutive columns
-  const bool cok = c < d;        // d % 4 == 0
+  auto merge = [&](auto first_chunk) {
 #pragma unroll
-  for (int f = 0; f < 4; ++f) {
-    f32x4 old[16];
+    for (int f = 0; f < FM; ++f)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = m0 + mp.row(f, r);
-      old[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (!first && cok && row < T) old[r] = *reinterpret_cast<const f32x4*>(Gs + (int64_t)row * d + c);
-    }
+      for (int i = 0; i < FN; i += VEC) {
+        const int c = n0 + mp.col(i);  // VEC consecutive columns
+        const bool cok = c < d;        // d % 4 == 0
+        const int cl = cok ? c : 0;    // the loads run unguarded, outside ones from a valid place
+        fvec old[16];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int lr = mp.row(f, r);
-      const int row = m0 + lr;
-      if (!cok || row >= T) continue;
-      const float so = sf[lr], sa = sf[256 + lr];
-      const f32x4 o = f32x4{acc[f][0][r], acc[f][1][r], acc[f][2][r], acc[f][3][r]} * so + old[r] * sa;
-      *reinterpret_cast<f32x4*>(Gs + (int64_t)row * d + c) = o;
-    }
-  }
+        for (int r = 0; r < 16; ++r) {
+          const int row = min(m0 + mp.row(f, r), T - 1);
+          if constexpr (!first_chunk) old[r] = *reinterpret_cast<const fvec*>(Gs + (int64_t)row * d + cl);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int lr = mp.row(f, r);
+          const int row = m0 + lr;
+          if (!cok || row >= T) continue;
+          fvec o = acc_vec<VEC>(acc[f], i, r) * sf[lr];
+          if constexpr (!first_chunk) o += old[r] * sf[BM + lr];
+          *reinterpret_cast<fvec*>(Gs + (int64_t)row * d + c) = o;
+        }
+      }
+  };
+  if (first) merge(std::true_type{});
+  else merge(std::false_type{});
 }
 
 template <class E, bool FAST>
@@ -484,16 +516,31 @@ __global__ __launch_bounds__(256, 1) void proj_chunk_kernel(
     const typename E::T* __restrict__ P, int64_t ldp, const typename E::T* __restrict__ Wc,
     int T, int d, int vc_valid, int nb, int bps, int blkw, int first, int nsplit,
     const float* __restrict__ fout, const float* __restrict__ alpha, float* __restrict__ G,
-    int64_t split_stride) {
+    int64_t split_stride, int nbig) {
   using TT = Tile<E>;
+  constexpr bool kQuarters = E::EPC == 8 && E::BM == 128;
+  constexpr int kEdge = kQuarters ? 256 : TT::BM;
   // tiles: (token rows) x (split, column); columns of one split are adjacent
-  const int ntm = (T + TT::BM - 1) / TT::BM, ntn = (d + TT::BN - 1) / TT::BN;
+  const int ntm = (T + kEdge - 1) / kEdge, ntn = (d + kEdge - 1) / kEdge;
+  const int per = kQuarters ? 2 * ntn : ntn;  // column tiles of one split
   int tm, tsn;
-  grouped_tile(xcd_remap(blockIdx.x, gridDim.x), ntm, ntn * nsplit, 8, tm, tsn);
-  const int sp = tsn / ntn;
-  const int m0 = tm * TT::BM, n0 = (tsn % ntn) * TT::BN;
+  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn * nsplit, tm, tsn);
+  const int sp = to_scalar(tsn / per);
+  const int m0 = tm * TT::BM, n0 = (tsn % per) * TT::BN;
   float* Gs = G + sp * split_stride;
-  if constexpr (E::EPC == 8) {
+  if constexpr (kQuarters) {
+    if (m0 >= T || n0 >= d) return;
+    __shared__ G2SSmem sm;
+    f32x16 acc[2][2];
+    zero_acc2s<true>(acc);
+    const int tpb = blkw / G2S::BK;
+    const int nkt = (vc_valid + G2S::BK - 1) / G2S::BK;
+    const int kt0 = min(sp * bps * tpb, nkt), kt1 = min(min(nb, (sp + 1) * bps) * tpb, nkt);
+    const Operand A{P + (int64_t)m0 * ldp, ldp, band_bytes(T - m0, ldp)};
+    const Operand B{Wc + n0, d, band_bytes(vc_valid, d, n0)};
+    gemm2s_mainloop<true>(sm, acc, A, B, T - m0, d - n0, vc_valid, kt0, kt1);
+    proj_epilogue2<128>(acc, AccMap2S<true>(), reinterpret_cast<float*>(sm.s), m0, n0, T, d, first, fout, alpha, Gs);
+  } else if constexpr (E::EPC == 8) {
     __shared__ G2Smem sm;
     f32x16 acc[4][4];
     zero_acc2(acc);
@@ -503,7 +550,7 @@ __global__ __launch_bounds__(256, 1) void proj_chunk_kernel(
     const Operand A{P + (int64_t)m0 * ldp, ldp, band_bytes(T - m0, ldp)};
     const Operand B{Wc + n0, d, band_bytes(vc_valid, d, n0)};
     gemm2_mainloop<true, FAST>(sm, acc, A, B, T - m0, d - n0, vc_valid, kt0, kt1);
-    proj_epilogue2(acc, sm, m0, n0, T, d, first, fout, alpha, Gs);
+    proj_epilogue2<256>(acc, AccMap2<true>(), reinterpret_cast<float*>(sm.s), m0, n0, T, d, first, fout, alpha, Gs);
   } else {
     __shared__ GemmSmem<E> sm;
     f32x4 acc[E::FM][E::FN];
@@ -612,59 +659,92 @@ __global__ __launch_bounds__(256) void finalize_vjp_kernel(
     if (e_ != hipSuccess) return e_;             \
   } while (0)
 
+// One GEMM launch of the E tiles [first tile, first tile + n) (see split_tile).
+template <class E>
+static void launch_logits(const OeLaunch& a, int v0, int vc_valid, int nbv, bool fast, int n, int nbig) {
+  using T = typename E::T;
+  hipStream_t st = (hipStream_t)a.stream;
+  const T* W = (const T*)a.W_U + (int64_t)v0 * a.d;
+  if (fast)
+    FPO_LAUNCH("logits_chunk", st,
+               logits_chunk_kernel<E, true><<<dim3(n), dim3(256), 0, st>>>(
+        (const T*)a.y, W, (int)a.T, (int)a.d, vc_valid, v0, a.ref, (T*)a.P, a.ldp, nbv, a.blk_m, a.blk_s, a.blk_i,
+        nbig));
+  else
+    FPO_LAUNCH("logits_chunk", st,
+               logits_chunk_kernel<E, false><<<dim3(n), dim3(256), 0, st>>>(
+        (const T*)a.y, W, (int)a.T, (int)a.d, vc_valid, v0, a.ref, (T*)a.P, a.ldp, nbv, a.blk_m, a.blk_s, a.blk_i,
+        nbig));
+}
+
+template <class E>
+static void launch_proj(const OeLaunch& a, int v0, int vc_valid, int nbv, bool first, bool fast, int n, int nbig) {
+  using T = typename E::T;
+  hipStream_t st = (hipStream_t)a.stream;
+  const T* W = (const T*)a.W_U + (int64_t)v0 * a.d;
+  const int bps = (nbv + a.nsplit - 1) / a.nsplit;
+  if (fast)
+    FPO_LAUNCH("proj_chunk", st,
+               proj_chunk_kernel<E, true><<<dim3(n), dim3(256), 0, st>>>(
+        (const T*)a.P, a.ldp, W, (int)a.T, (int)a.d, vc_valid, nbv, bps, Tile<E>::SB, first, a.nsplit, a.fout,
+        a.alpha, a.G, a.T * a.d, nbig));
+  else
+    FPO_LAUNCH("proj_chunk", st,
+               proj_chunk_kernel<E, false><<<dim3(n), dim3(256), 0, st>>>(
+        (const T*)a.P, a.ldp, W, (int)a.T, (int)a.d, vc_valid, nbv, bps, Tile<E>::SB, first, a.nsplit, a.fout,
+        a.alpha, a.G, a.T * a.d, nbig));
+}
+
 template <class E>
 static hipError_t run_output_error(const OeLaunch& a) {
   using T = typename E::T;
   using TT = Tile<E>;
+  constexpr bool kBf16 = E::EPC == 8;
   hipStream_t st = (hipStream_t)a.stream;
   const T* x = (const T*)a.h_final;
   const T* gamma = (const T*)a.gamma;
   const T* W = (const T*)a.W_U;
-  T* y = (T*)a.y;
   T* P = (T*)a.P;
   FPO_LAUNCH("rms_forward", st,
              rms_forward_kernel<T><<<dim3((unsigned)a.T), dim3(256), 0, st>>>(
-      x, gamma, (int)a.d, a.eps, y, W, a.targets, (int)a.V, a.ref, a.zt, a.bad_targets));
+      x, gamma, (int)a.d, a.eps, (T*)a.y, W, a.targets, (int)a.V, a.ref, a.zt, a.bad_targets));
   FPO_CHECK_LAUNCH();
-  const int gm = (int)((a.T + TT::BM - 1) / TT::BM);
   for (int c = 0; c < a.nchunk; ++c) {
     int64_t v0, width;
     chunk_span(a.V, a.nchunk, a.cw, a.cq, a.nwide, c, &v0, &width);
     const int vc_valid = (int)width;
-    const int gn = (vc_valid + TT::BN - 1) / TT::BN;
-    const int nbv = (vc_valid + TT::WTN - 1) / TT::WTN;  // blocks holding a valid column
-    // whole 256 x 256 tiles and 64-deep K tiles: the copy form without bounds
-    const bool fast_l = vc_valid % TT::BM == 0 && a.T % TT::BN == 0 && a.d % 64 == 0;
-    if (fast_l)
-      FPO_LAUNCH("logits_chunk", st,
-                 logits_chunk_kernel<E, true><<<dim3(gm * gn), dim3(256), 0, st>>>(
-          y, W + v0 * a.d, (int)a.T, (int)a.d, vc_valid, (int)v0, a.ref, P, a.ldp, nbv, a.blk_m, a.blk_s,
-          a.blk_i));
-    else
-      FPO_LAUNCH("logits_chunk", st,
-                 logits_chunk_kernel<E, false><<<dim3(gm * gn), dim3(256), 0, st>>>(
-          y, W + v0 * a.d, (int)a.T, (int)a.d, vc_valid, (int)v0, a.ref, P, a.ldp, nbv, a.blk_m, a.blk_s,
-          a.blk_i));
-    FPO_CHECK_LAUNCH();
+    const int nbv = (vc_valid + TT::SB - 1) / TT::SB;  // blocks holding a valid column
+    {
+      const int64_t tiles = ceil_div(a.T, TT::BM) * ceil_div(vc_valid, TT::BN);
+      if constexpr (kBf16) {
+        const int nbig = (int)big_tiles(a.T, vc_valid, a.d, 1).nbig;
+        // whole 256 x 256 tiles and 64-deep K tiles: the copy form without bounds
+        const bool fast = vc_valid % TT::BM == 0 && a.T % TT::BN == 0 && a.d % 64 == 0;
+        if (nbig) launch_logits<E>(a, (int)v0, vc_valid, nbv, fast, nbig, 0);
+        if (nbig < tiles) launch_logits<TileBF16S>(a, (int)v0, vc_valid, nbv, false, 4 * ((int)tiles - nbig), nbig);
+      } else {
+        launch_logits<E>(a, (int)v0, vc_valid, nbv, false, (int)tiles, 0);
+      }
+      FPO_CHECK_LAUNCH();
+    }
     FPO_LAUNCH("chunk_stats", st,
                chunk_stats_kernel<T><<<dim3((unsigned)((a.T + 3) / 4)), dim3(256), 0, st>>>(
         (int)a.T, nbv, c == 0, a.blk_m, a.blk_s, a.blk_i, a.ref, a.runM, a.runS, a.runA, a.fout, a.alpha,
-        P, a.ldp, TT::WTN));
+        P, a.ldp, TT::SB));
     FPO_CHECK_LAUNCH();
-    const int bps = (nbv + a.nsplit - 1) / a.nsplit;
-    const bool fast_p = a.T % TT::BM == 0 && a.d % TT::BN == 0 && vc_valid % 64 == 0;
-    const dim3 gp(gm * (unsigned)((a.d + TT::BN - 1) / TT::BN) * a.nsplit);
-    if (fast_p)
-      FPO_LAUNCH("proj_chunk", st,
-                 proj_chunk_kernel<E, true><<<gp, dim3(256), 0, st>>>(
-          P, a.ldp, W + v0 * a.d, (int)a.T, (int)a.d, vc_valid, nbv, bps, TT::WTN, c == 0, a.nsplit,
-          a.fout, a.alpha, a.G, a.T * a.d));
-    else
-      FPO_LAUNCH("proj_chunk", st,
-                 proj_chunk_kernel<E, false><<<gp, dim3(256), 0, st>>>(
-          P, a.ldp, W + v0 * a.d, (int)a.T, (int)a.d, vc_valid, nbv, bps, TT::WTN, c == 0, a.nsplit,
-          a.fout, a.alpha, a.G, a.T * a.d));
-    FPO_CHECK_LAUNCH();
+    {
+      const int64_t tiles = ceil_div(a.T, TT::BM) * ceil_div(a.d, TT::BN) * a.nsplit;
+      if constexpr (kBf16) {
+        const int nbig = (int)big_tiles(a.T, a.d, ceil_div(nbv, a.nsplit) * TT::SB, a.nsplit, a.d).nbig;
+        const bool fast = a.T % TT::BM == 0 && a.d % TT::BN == 0 && vc_valid % 64 == 0;
+        if (nbig) launch_proj<E>(a, (int)v0, vc_valid, nbv, c == 0, fast, nbig, 0);
+        if (nbig < tiles)
+          launch_proj<TileBF16S>(a, (int)v0, vc_valid, nbv, c == 0, false, 4 * ((int)tiles - nbig), nbig);
+      } else {
+        launch_proj<E>(a, (int)v0, vc_valid, nbv, c == 0, false, (int)tiles, 0);
+      }
+      FPO_CHECK_LAUNCH();
+    }
   }
   FPO_LAUNCH("finalize_vjp", st,
              finalize_vjp_kernel<T><<<dim3((unsigned)a.T), dim3(256), 0, st>>>(

@@ -16,10 +16,12 @@
 // overlapping the GEMM launches that follow.
 #include "gemm.hpp"
 #include "gemm2.hpp"
+#include "gemm2s.hpp"
 #include "launch.hpp"
 #include "prof.hpp"
 
 #include <mutex>
+#include <type_traits>
 
 namespace fpo {
 
@@ -218,41 +220,55 @@ __device__ __forceinline__ void outer_epilogue(VA (&acc)[FM][FN], const Map& mp,
 // the loads overlap; every lane's 4 columns are consecutive.
 // With Cb the tile is stored rounded to bf16 (RNE) and the partial norms and
 // dot products are of the rounded values.
-__device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[4][4], int m0, int n0, int M,
+__device__ __forceinline__ float dot(f32x4 a, f32x4 b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
+__device__ __forceinline__ float dot(float a, float b) { return a * b; }
+
+template <class Map, int FM, int FN>
+__device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[FM][FN], const Map& mp, int m0, int n0, int M,
                                                 int N, float scale, float* __restrict__ C,
                                                 uint16_t* __restrict__ Cb,
                                                 const float* __restrict__ R, double* red,
                                                 double* __restrict__ part_out) {
-  const AccMap2<true> mp;
-  const int c = n0 + mp.col(0);
-  const bool cok = c < N;  // N % 4 == 0: a lane's columns are all in or all out
+  constexpr int VEC = Map::VEC;
+  using fvec = typename FVec<VEC>::T;
   float ss = 0.f, dt = 0.f, rr = 0.f;
 #pragma unroll
-  for (int f = 0; f < 4; ++f) {
-    f32x4 q[16];
-    if (R) {
+  for (int i = 0; i < FN; i += VEC) {
+    const int c = n0 + mp.col(i);  // VEC consecutive columns
+    const bool cok = c < N;        // N % 4 == 0: they are all in or all out
+#pragma unroll
+    for (int f = 0; f < FM; ++f) {
+      fvec q[16];
+      if (R) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = m0 + mp.row(f, r);
+          q[r] = fvec{};
+          if (cok && row < M) q[r] = *reinterpret_cast<const fvec*>(R + (int64_t)row * N + c);
+        }
+      }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int row = m0 + mp.row(f, r);
-        q[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (cok && row < M) q[r] = *reinterpret_cast<const f32x4*>(R + (int64_t)row * N + c);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = m0 + mp.row(f, r);
-      if (!cok || row >= M) continue;
-      f32x4 v = f32x4{acc[f][0][r], acc[f][1][r], acc[f][2][r], acc[f][3][r]} * scale;
-      if (Cb) {
-        const u32x2 h = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
-        *reinterpret_cast<u32x2*>(Cb + (int64_t)row * N + c) = h;
-        v = f32x4{bf16_lo(h.x), bf16_hi(h.x), bf16_lo(h.y), bf16_hi(h.y)};
-      }
-      if (C) *reinterpret_cast<f32x4*>(C + (int64_t)row * N + c) = v;
-      ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-      if (R) {
-        dt += v.x * q[r].x + v.y * q[r].y + v.z * q[r].z + v.w * q[r].w;
-        rr += q[r].x * q[r].x + q[r].y * q[r].y + q[r].z * q[r].z + q[r].w * q[r].w;
+        if (!cok || row >= M) continue;
+        fvec v = acc_vec<VEC>(acc[f], i, r) * scale;
+        if (Cb) {
+          if constexpr (VEC == 4) {
+            const u32x2 h = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
+            *reinterpret_cast<u32x2*>(Cb + (int64_t)row * N + c) = h;
+            v = f32x4{bf16_lo(h.x), bf16_hi(h.x), bf16_lo(h.y), bf16_hi(h.y)};
+          } else {
+            const uint16_t h = to_bf16(v);
+            Cb[(int64_t)row * N + c] = h;
+            v = bf16_to_f32(h);
+          }
+        }
+        if (C) *reinterpret_cast<fvec*>(C + (int64_t)row * N + c) = v;
+        ss += dot(v, v);
+        if (R) {
+          dt += dot(v, q[r]);
+          rr += dot(q[r], q[r]);
+        }
       }
     }
   }
@@ -270,12 +286,18 @@ __device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[4][4], int m
   }
 }
 
+// Partials: tile ids run over (matrix, tile) in dispatch order; big tile g has
+// slot g, the quarters of a later tile four slots each (part_slot).
+__host__ __device__ inline int64_t part_slot(int64_t g, int64_t nbig) { return g < nbig ? g : 4 * g - 3 * nbig; }
+
 template <class E, bool FAST>
 __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, int N, int K,
                                                        int64_t lda, int64_t ldb, float scale,
-                                                       double* __restrict__ part) {
+                                                       double* __restrict__ part, int nbig) {
   using TT = Tile<E>;
   using T = typename E::T;
+  constexpr bool kQuarters = E::EPC == 8 && E::BM == 128;
+  constexpr int kEdge = kQuarters ? 256 : TT::BM;
   __shared__ double red[12];
   // one flat grid over (matrix, tile), matrix-major in dispatch order, each
   // matrix's tiles spread over the 8 XCDs (a contiguous group per XCD), so
@@ -283,24 +305,41 @@ __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, in
   // than on eight different ones (how closely depends on dispatch timing: the
   // 36-layer diagnostic launch reads 65-91 GB beyond L2 from run to run, for
   // 14.5 GB of operands, which the Infinity Cache serves)
-  const int ntm = (M + TT::BM - 1) / TT::BM, ntn = (N + TT::BN - 1) / TT::BN;
+  const int ntm = (M + kEdge - 1) / kEdge, ntn = (N + kEdge - 1) / kEdge;
   const int ntiles = ntm * ntn;
-  const int mat = blockIdx.x / ntiles;
-  const int tile = xcd_remap(blockIdx.x - mat * ntiles, ntiles);
+  // quarters: the tiles from nbig on, four workgroups each, a contiguous range of
+  // them per XCD over the whole grid (whose tiles are then taken in order)
+  const int id = kQuarters ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+  const int g = kQuarters ? nbig + (id >> 2) : id;
+  const int mat = g / ntiles, loc = g - mat * ntiles;
+  const int tile = !kQuarters || nbig > mat * ntiles ? xcd_remap(loc, ntiles) : loc;
   int tm, tn;
   grouped_tile(tile, ntm, ntn, 8, tm, tn);
-  const int m0 = tm * TT::BM, n0 = tn * TT::BN;
+  const int sub = kQuarters ? id & 3 : 0;
+  const int m0 = tm * kEdge + (sub & 1) * 128, n0 = tn * kEdge + (sub >> 1) * 128;
   const T* Am = (const T*)args.A[mat];
   const T* Bm = (const T*)args.B[mat];
-  double* po = part + ((int64_t)mat * ntiles + tm + (int64_t)tn * ntm) * 3;
-  if constexpr (E::EPC == 8) {
+  double* po = part + (part_slot(g, nbig) + sub) * 3;
+  if constexpr (kQuarters) {
+    if (m0 >= M || n0 >= N) {  // outside a ragged matrix
+      if (threadIdx.x < 3) po[threadIdx.x] = 0.0;
+      return;
+    }
+    __shared__ G2SSmem sm;
+    f32x16 acc[2][2];
+    zero_acc2s<true>(acc);
+    const Operand A{Am + (int64_t)m0 * lda, lda, band_bytes(M - m0, lda)};
+    const Operand B{Bm + n0, ldb, band_bytes(K, ldb, n0)};
+    gemm2s_mainloop<true>(sm, acc, A, B, M - m0, N - n0, K, 0, (K + G2S::BK - 1) / G2S::BK);
+    outer_epilogue2(acc, AccMap2S<true>(), m0, n0, M, N, scale, args.C[mat], args.Cb[mat], args.R[mat], red, po);
+  } else if constexpr (E::EPC == 8) {
     __shared__ G2Smem sm;
     f32x16 acc[4][4];
     zero_acc2(acc);
     const Operand A{Am + (int64_t)m0 * lda, lda, band_bytes(M - m0, lda)};
     const Operand B{Bm + n0, ldb, band_bytes(K, ldb, n0)};
     gemm2_mainloop<true, FAST>(sm, acc, A, B, M - m0, N - n0, K, 0, (K + G2::BK - 1) / G2::BK);
-    outer_epilogue2(acc, m0, n0, M, N, scale, args.C[mat], args.Cb[mat], args.R[mat], red, po);
+    outer_epilogue2(acc, AccMap2<true>(), m0, n0, M, N, scale, args.C[mat], args.Cb[mat], args.R[mat], red, po);
   } else {
     __shared__ GemmSmem<E> sm;
     f32x4 acc[E::FM][E::FN];
@@ -352,46 +391,57 @@ __device__ __forceinline__ void errh_epilogue(VA (&acc)[FM][FN], const Map& mp, 
 // bf16 form: per fragment and group of 4 consecutive tokens, the lane's 4
 // consecutive columns of q and u are loaded as 8-byte runs (all 8 loads before
 // use), and dq^T, du^T go out as 8-byte runs of 4 tokens.
-__device__ __forceinline__ void errh_epilogue2(const f32x16 (&acc)[4][4], int m0, int n0,
+template <class Map, int FM, int FN>
+__device__ __forceinline__ void errh_epilogue2(const f32x16 (&acc)[FM][FN], const Map& mp, int m0, int n0,
                                                const uint16_t* __restrict__ q,
                                                const uint16_t* __restrict__ u, int T, int Tp,
                                                int d_ff, uint16_t* __restrict__ dq_T,
                                                uint16_t* __restrict__ du_T) {
-  const AccMap2<true> mp;
-  const int j0 = n0 + mp.col(0);
-  if (j0 >= d_ff) return;  // d_ff % 4 == 0: the lane's 4 columns are all in or all out
+  constexpr int VEC = Map::VEC;
+  using hvec = typename std::conditional<VEC == 4, u32x2, uint16_t>::type;
 #pragma unroll
-  for (int f = 0; f < 4; ++f)
+  for (int f = 0; f < FM; ++f)
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int t0 = m0 + mp.row(f, 4 * g);  // tokens t0..t0+3
-      if (t0 >= Tp) continue;                // Tp % 4 == 0
-      u32x2 qv[4], uv[4];
+    for (int i0 = 0; i0 < FN; i0 += VEC) {
+      const int j0 = n0 + mp.col(i0);  // VEC consecutive columns
+      if (j0 >= d_ff) continue;        // d_ff % 4 == 0: they are all in or all out
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        qv[r] = u32x2{0u, 0u};
-        uv[r] = u32x2{0u, 0u};
-        if (t0 + r < T) {
-          qv[r] = *reinterpret_cast<const u32x2*>(q + (int64_t)(t0 + r) * d_ff + j0);
-          uv[r] = *reinterpret_cast<const u32x2*>(u + (int64_t)(t0 + r) * d_ff + j0);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float vq[4], vu[4];
+      for (int g = 0; g < 4; ++g) {
+        const int t0 = m0 + mp.row(f, 4 * g);  // tokens t0..t0+3
+        if (t0 >= Tp) continue;                // Tp % 4 == 0
+        hvec qv[4], uv[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const uint32_t qw = qv[r][i >> 1], uw = uv[r][i >> 1];
-          const float qq = (i & 1) ? bf16_hi(qw) : bf16_lo(qw);
-          const float uu = (i & 1) ? bf16_hi(uw) : bf16_lo(uw);
-          const float e = acc[f][i][4 * g + r];
-          const float sg = 1.0f / (1.0f + __expf(-qq));
-          const bool in = t0 + r < T;
-          vu[r] = in ? e * qq * sg : 0.f;
-          vq[r] = in ? e * uu * sg * (1.0f + qq * (1.0f - sg)) : 0.f;
+          qv[r] = hvec{};
+          uv[r] = hvec{};
+          if (t0 + r < T) {
+            qv[r] = *reinterpret_cast<const hvec*>(q + (int64_t)(t0 + r) * d_ff + j0);
+            uv[r] = *reinterpret_cast<const hvec*>(u + (int64_t)(t0 + r) * d_ff + j0);
+          }
         }
-        st4<uint16_t>(dq_T + (int64_t)(j0 + i) * Tp + t0, 0, f32x4{vq[0], vq[1], vq[2], vq[3]});
-        st4<uint16_t>(du_T + (int64_t)(j0 + i) * Tp + t0, 0, f32x4{vu[0], vu[1], vu[2], vu[3]});
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          float vq[4], vu[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            float qq, uu;
+            if constexpr (VEC == 4) {
+              const uint32_t qw = qv[r][i >> 1], uw = uv[r][i >> 1];
+              qq = (i & 1) ? bf16_hi(qw) : bf16_lo(qw);
+              uu = (i & 1) ? bf16_hi(uw) : bf16_lo(uw);
+            } else {
+              qq = bf16_to_f32(qv[r]);
+              uu = bf16_to_f32(uv[r]);
+            }
+            const float e = acc[f][i0 + i][4 * g + r];
+            const float sg = 1.0f / (1.0f + __expf(-qq));
+            const bool in = t0 + r < T;
+            vu[r] = in ? e * qq * sg : 0.f;
+            vq[r] = in ? e * uu * sg * (1.0f + qq * (1.0f - sg)) : 0.f;
+          }
+          st4<uint16_t>(dq_T + (int64_t)(j0 + i) * Tp + t0, 0, f32x4{vq[0], vq[1], vq[2], vq[3]});
+          st4<uint16_t>(du_T + (int64_t)(j0 + i) * Tp + t0, 0, f32x4{vu[0], vu[1], vu[2], vu[3]});
+        }
       }
     }
 }
@@ -486,13 +536,24 @@ __global__ __launch_bounds__(256, 1) void errh_kernel(const typename E::T* __res
                                                       const typename E::T* __restrict__ u, int T,
                                                       int Tp, int d, int d_ff,
                                                       typename E::T* __restrict__ dq_T,
-                                                      typename E::T* __restrict__ du_T) {
+                                                      typename E::T* __restrict__ du_T, int nbig) {
   using TT = Tile<E>;
-  const int ntm = (Tp + TT::BM - 1) / TT::BM, ntn = (d_ff + TT::BN - 1) / TT::BN;
+  constexpr bool kQuarters = E::EPC == 8 && E::BM == 128;
+  constexpr int kEdge = kQuarters ? 256 : TT::BM;
+  const int ntm = (Tp + kEdge - 1) / kEdge, ntn = (d_ff + kEdge - 1) / kEdge;
   int tm, tn;
-  grouped_tile(xcd_remap(blockIdx.x, gridDim.x), ntm, ntn, 8, tm, tn);
+  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn, tm, tn);
   const int m0 = tm * TT::BM, n0 = tn * TT::BN;
-  if constexpr (E::EPC == 8) {
+  if constexpr (kQuarters) {
+    if (m0 >= Tp || n0 >= d_ff) return;
+    __shared__ G2SSmem sm;
+    f32x16 acc[2][2];
+    zero_acc2s<true>(acc);
+    const Operand A{g + (int64_t)m0 * d, d, band_bytes(T - m0, d)};
+    const Operand B{W3i + n0, d_ff, band_bytes(d, d_ff, n0)};
+    gemm2s_mainloop<true>(sm, acc, A, B, T - m0, d_ff - n0, d, 0, (d + G2S::BK - 1) / G2S::BK);
+    errh_epilogue2(acc, AccMap2S<true>(), m0, n0, q, u, T, Tp, d_ff, dq_T, du_T);
+  } else if constexpr (E::EPC == 8) {
     __shared__ G2Smem sm;
     f32x16 acc[4][4];
     zero_acc2(acc);
@@ -502,7 +563,7 @@ __global__ __launch_bounds__(256, 1) void errh_kernel(const typename E::T* __res
     if constexpr (FAST)
       errh_epilogue_lds(acc, sm, m0, n0, q, u, Tp, d_ff, dq_T, du_T);
     else
-      errh_epilogue2(acc, m0, n0, q, u, T, Tp, d_ff, dq_T, du_T);
+      errh_epilogue2(acc, AccMap2<true>(), m0, n0, q, u, T, Tp, d_ff, dq_T, du_T);
   } else {
     __shared__ GemmSmem<E> sm;
     f32x4 acc[E::FM][E::FN];
@@ -514,19 +575,20 @@ __global__ __launch_bounds__(256, 1) void errh_kernel(const typename E::T* __res
 }
 
 // Fixed-order float64 sums of one matrix's tile partials per workgroup:
-// ||C||^2 (into sumsq[mat_base + mat]) and, against a reference R, <C, R>,
+// ||C||^2 (into sumsq[mat_base + mat * mat_step]) and, against a reference R, <C, R>,
 // ||R||^2 and cos = <C, R> / (||C|| ||R||) (0 when either norm is 0; eq. cosine).
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const double* __restrict__ part,
-                                                           int ntiles, int mat_base,
+                                                           int ntiles, int nbig, int mat_base, int mat_step,
                                                            double* __restrict__ sumsq,
                                                            double* __restrict__ dot,
                                                            double* __restrict__ refsq,
                                                            float* __restrict__ cos) {
   __shared__ double red[16];
   const int mat = blockIdx.x;
-  const double* p = part + (int64_t)mat * ntiles * 3;
+  const int64_t s0 = part_slot((int64_t)mat * ntiles, nbig), s1 = part_slot((int64_t)(mat + 1) * ntiles, nbig);
+  const double* p = part + s0 * 3;
   double a = 0.0, b = 0.0, c = 0.0;
-  for (int t = threadIdx.x; t < ntiles; t += 256) {
+  for (int t = threadIdx.x; t < s1 - s0; t += 256) {
     a += p[3 * t];
     b += p[3 * t + 1];
     c += p[3 * t + 2];
@@ -535,7 +597,7 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const double* __restr
   b = block_sum_d(b, red);
   c = block_sum_d(c, red);
   if (threadIdx.x == 0) {
-    if (sumsq) sumsq[mat_base + mat] = a;
+    if (sumsq) sumsq[mat_base + mat * mat_step] = a;
     if (dot) dot[mat] = b;
     if (refsq) refsq[mat] = c;
     if (cos) cos[mat] = (a == 0.0 || c == 0.0) ? 0.f : (float)(b / sqrt(a * c));
@@ -609,23 +671,54 @@ static bool whole_tiles(int64_t M, int64_t N, int64_t K) {
   return M % 256 == 0 && N % 256 == 0 && K % 64 == 0;
 }
 
+// The outer products of matrices m0 .. m0 + mats - 1 of a list of `of` (M x N over
+// K); returns how many of their tiles went as 256 x 256 ones (the layout of the
+// partials; see part_slot). That is decided for the list as one launch, whether or
+// not it is one: a matrix's tiles, and with them the order of its norm's sum, do
+// not depend on what is launched together.
 template <class E>
-static void launch_outer(dim3 grid, hipStream_t st, const OuterArgs& oa, int M, int N, int K, int64_t lda,
-                         int64_t ldb, float scale, double* part) {
-  if (whole_tiles(M, N, K))
-    outer_kernel<E, true><<<grid, dim3(256), 0, st>>>(oa, M, N, K, lda, ldb, scale, part);
-  else
-    outer_kernel<E, false><<<grid, dim3(256), 0, st>>>(oa, M, N, K, lda, ldb, scale, part);
+static int launch_outer(int m0, int mats, int of, hipStream_t st, const OuterArgs& oa, int M, int N, int K,
+                        int64_t lda, int64_t ldb, float scale, double* part) {
+  const int nt = (int)pseudograd_tiles(E::BM, M, N), n = nt * mats;
+  int nbig = n;
+  if constexpr (E::EPC == 8)
+    nbig = (int)std::max<int64_t>(0, std::min<int64_t>(n, big_tiles(M, N, K, of, ldb).nbig - (int64_t)m0 * nt));
+  if (nbig) {
+    if (whole_tiles(M, N, K))
+      FPO_LAUNCH("outer", st, outer_kernel<E, true><<<dim3(nbig), dim3(256), 0, st>>>(
+          oa, M, N, K, lda, ldb, scale, part, nbig));
+    else
+      FPO_LAUNCH("outer", st, outer_kernel<E, false><<<dim3(nbig), dim3(256), 0, st>>>(
+          oa, M, N, K, lda, ldb, scale, part, nbig));
+  }
+  if constexpr (E::EPC == 8) {
+    if (nbig < n)
+      FPO_LAUNCH("outer", st, outer_kernel<TileBF16S, false><<<dim3(4 * (n - nbig)), dim3(256), 0, st>>>(
+          oa, M, N, K, lda, ldb, scale, part, nbig));
+  }
+  return nbig;
 }
 
 template <class E>
-static void launch_errh(dim3 grid, hipStream_t st, const typename E::T* g, const typename E::T* W3i,
+static void launch_errh(hipStream_t st, const typename E::T* g, const typename E::T* W3i,
                         const typename E::T* q, const typename E::T* u, int T, int Tp, int d, int d_ff,
                         typename E::T* dq_T, typename E::T* du_T) {
-  if (whole_tiles(T, d_ff, d))
-    errh_kernel<E, true><<<grid, dim3(256), 0, st>>>(g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T);
-  else
-    errh_kernel<E, false><<<grid, dim3(256), 0, st>>>(g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T);
+  const int n = (int)pseudograd_tiles(E::BM, Tp, d_ff);
+  int nbig = n;
+  if constexpr (E::EPC == 8) nbig = (int)big_tiles(Tp, d_ff, d, 1, d_ff).nbig;
+  if (nbig) {
+    if (whole_tiles(T, d_ff, d))
+      FPO_LAUNCH("errh", st, errh_kernel<E, true><<<dim3(nbig), dim3(256), 0, st>>>(
+          g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T, 0));
+    else
+      FPO_LAUNCH("errh", st, errh_kernel<E, false><<<dim3(nbig), dim3(256), 0, st>>>(
+          g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T, 0));
+  }
+  if constexpr (E::EPC == 8) {
+    if (nbig < n)
+      FPO_LAUNCH("errh", st, errh_kernel<TileBF16S, false><<<dim3(4 * (n - nbig)), dim3(256), 0, st>>>(
+          g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T, nbig));
+  }
 }
 
 template <class E>
@@ -647,23 +740,18 @@ static hipError_t run_pseudograd(const PgLaunch& a) {
       oa.Cb[l] = a.dW3_bf16[l];
       oa.R[l] = a.ref[l];
     }
-    FPO_LAUNCH("outer", st,
-               launch_outer<E>(dim3(ntiles * a.L), st, oa, (int)a.d, (int)a.d_ff, (int)a.T, a.Tp, a.d_ff,
-                               a.scale, a.part));
+    const int nbig = launch_outer<E>(0, a.L, a.L, st, oa, (int)a.d, (int)a.d_ff, (int)a.T, a.Tp, a.d_ff, a.scale, a.part);
     FPO_CHECK_LAUNCH();
     FPO_LAUNCH("reduce_parts", st,
-               reduce_parts_kernel<<<dim3(a.L), dim3(256), 0, st>>>(a.part, ntiles, 0, a.sumsq, a.ref_dot,
+               reduce_parts_kernel<<<dim3(a.L), dim3(256), 0, st>>>(a.part, ntiles, nbig, 0, 1, a.sumsq, a.ref_dot,
                                                          a.ref_sumsq, a.ref_cos));
     FPO_CHECK_LAUNCH();
   }
   if (!a.full_mlp) return hipSuccess;
   // W1/W2 signals through W3_init (eq. errh), one layer at a time
   for (int l = 0; l < a.L; ++l) {
-    FPO_LAUNCH("errh", st,
-               launch_errh<E>(dim3((unsigned)(((a.Tp + TT::BM - 1) / TT::BM) * ((a.d_ff + TT::BN - 1) / TT::BN))),
-                              st, signal_rows<T>(a, l), (const T*)a.W3i[l], (const T*)a.q[l],
-                              (const T*)a.u[l], (int)a.T, (int)a.Tp, (int)a.d, (int)a.d_ff, (T*)a.dq_T,
-                              (T*)a.du_T));
+    launch_errh<E>(st, signal_rows<T>(a, l), (const T*)a.W3i[l], (const T*)a.q[l], (const T*)a.u[l], (int)a.T,
+                   (int)a.Tp, (int)a.d, (int)a.d_ff, (T*)a.dq_T, (T*)a.du_T);
     FPO_CHECK_LAUNCH();
     OuterArgs oa{};
     oa.A[0] = a.dq_T;
@@ -672,19 +760,13 @@ static hipError_t run_pseudograd(const PgLaunch& a) {
     oa.A[1] = a.du_T;
     oa.B[1] = a.x_in[l];
     oa.C[1] = a.dW2[l];
-    FPO_LAUNCH("outer", st,
-               launch_outer<E>(dim3(ntiles2 * 2), st, oa, (int)a.d_ff, (int)a.d, (int)a.T, a.Tp, a.d, a.scale,
-                               a.part));
+    const int nbig = launch_outer<E>(0, 2, 2, st, oa, (int)a.d_ff, (int)a.d, (int)a.T, a.Tp, a.d, a.scale, a.part);
     FPO_CHECK_LAUNCH();
     // matrices W1(l) and W2(l) sit at a.L + l and 2 a.L + l of sumsq
     if (a.sumsq) {
       FPO_LAUNCH("reduce_parts", st,
-                 reduce_parts_kernel<<<dim3(1), dim3(256), 0, st>>>(a.part, ntiles2, a.L + l, a.sumsq,
+                 reduce_parts_kernel<<<dim3(2), dim3(256), 0, st>>>(a.part, ntiles2, nbig, a.L + l, a.L, a.sumsq,
                                                          nullptr, nullptr, nullptr));
-      FPO_CHECK_LAUNCH();
-      FPO_LAUNCH("reduce_parts", st,
-                 reduce_parts_kernel<<<dim3(1), dim3(256), 0, st>>>(a.part + (int64_t)ntiles2 * 3, ntiles2,
-                                                         2 * a.L + l, a.sumsq, nullptr, nullptr, nullptr));
       FPO_CHECK_LAUNCH();
     }
   }
@@ -755,7 +837,6 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
   hipError_t e;
   if ((e = prepare_signals<uint16_t>(a, st)) != hipSuccess) return e;
   const int ntiles = (int)pseudograd_tiles(a.tile, a.d, a.d_ff);
-  const int ntiles2 = (int)pseudograd_tiles(a.tile, a.d_ff, a.d);
   // matrix m: W3 of layer m (m < L), then W1 and W2 of layer l at L + l and
   // 2 L + l; its update blocks start at the sum of the earlier matrices'
   // blocks. Tile partials have a region per matrix (the side stream reads them
@@ -766,18 +847,21 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
   int64_t blk_base[kMaxMats + 1];
   blk_base[0] = 0;
   for (int m = 0; m < nm; ++m) blk_base[m + 1] = blk_base[m] + update_blocks(u.numel[m]);
-  auto tpart = [&](int slot) { return a.part + (int64_t)slot * ntiles * 3; };
-  // the norm reduction and the update of matrix m (partials in `slot`) on the
-  // side stream, after the launch just enqueued on st; `alone`: no GEMM
-  // follows to share the CUs
-  auto release = [&](int m, int slot, int nt, bool ref, bool alone) -> hipError_t {
+  auto tpart = [&](int slot) { return a.part + (int64_t)slot * part_slot(ntiles, 0) * 3; };
+  // the norm reductions of the `mats` matrices base, base + step, .. of one
+  // launch (partials from `slot` on), on the side stream
+  auto reduce = [&](int mats, int slot, int nbig, int base, int step, bool ref) -> hipError_t {
     FPO_LAUNCH("reduce_parts", side,
-               reduce_parts_kernel<<<dim3(1), dim3(256), 0, side>>>(
-        tpart(slot), nt, m, a.sumsq, ref && a.ref_dot ? a.ref_dot + m : nullptr,
-        ref && a.ref_sumsq ? a.ref_sumsq + m : nullptr, ref && a.ref_cos ? a.ref_cos + m : nullptr));
+               reduce_parts_kernel<<<dim3(mats), dim3(256), 0, side>>>(
+        tpart(slot), ntiles, nbig, base, step, a.sumsq, ref && a.ref_dot ? a.ref_dot + base : nullptr,
+        ref && a.ref_sumsq ? a.ref_sumsq + base : nullptr, ref && a.ref_cos ? a.ref_cos + base : nullptr));
     FPO_CHECK_LAUNCH();
-    // one workgroup per CU beside the next GEMM launch; the last updates run
-    // alone and take the whole machine
+    return hipSuccess;
+  };
+  // the update of matrix m on the side stream: one workgroup per CU beside the
+  // next GEMM launch; `alone`: no GEMM follows to share the CUs, the update takes
+  // the whole machine
+  auto update = [&](int m, bool alone) -> hipError_t {
     return launch_update_blocks(u, m, blk_base[m], side, alone ? 0 : cus);
   };
   auto handoff = [&]() -> hipError_t {
@@ -792,25 +876,22 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
     oa.C[0] = a.dW3[l];
     oa.Cb[0] = a.dW3_bf16[l];
     oa.R[0] = a.ref[l];
-    FPO_LAUNCH("outer", st,
-               launch_outer<TileBF16>(dim3(ntiles), st, oa, (int)a.d, (int)a.d_ff, (int)a.T, a.Tp, a.d_ff,
-                                      a.scale, tpart(l)));
+    const int nbig = launch_outer<TileBF16>(l, 1, a.L, st, oa, (int)a.d, (int)a.d_ff, (int)a.T, a.Tp, a.d_ff, a.scale,
+                                            tpart(l));
     FPO_CHECK_LAUNCH();
     // layer l's tiles are complete: its norm reduction and update follow on the
     // side stream, so the next layer's outer products start right away
     if ((e = handoff()) != hipSuccess) return e;
-    if ((e = release(l, l, ntiles, true, !a.full_mlp && l + 1 == a.L)) != hipSuccess) return e;
+    if ((e = reduce(1, l, nbig, l, 1, true)) != hipSuccess) return e;
+    if ((e = update(l, !a.full_mlp && l + 1 == a.L)) != hipSuccess) return e;
   }
   // full MLP: W1/W2 signals through W3_init (eq. errh), then both outer
   // products of the layer in one launch, their updates released together
   for (int l = 0; a.full_mlp && l < a.L; ++l) {
-    FPO_LAUNCH("errh", st,
-               launch_errh<TileBF16>(dim3((unsigned)(((a.Tp + 255) / 256) * ((a.d_ff + 255) / 256))), st,
-                                     signal_rows<uint16_t>(a, l), (const uint16_t*)a.W3i[l],
-                                     (const uint16_t*)a.q[l], (const uint16_t*)a.u[l], (int)a.T, (int)a.Tp,
-                                     (int)a.d, (int)a.d_ff, (uint16_t*)a.dq_T, (uint16_t*)a.du_T));
+    launch_errh<TileBF16>(st, signal_rows<uint16_t>(a, l), (const uint16_t*)a.W3i[l], (const uint16_t*)a.q[l],
+                          (const uint16_t*)a.u[l], (int)a.T, (int)a.Tp, (int)a.d, (int)a.d_ff, (uint16_t*)a.dq_T,
+                          (uint16_t*)a.du_T);
     FPO_CHECK_LAUNCH();
-    const int m1 = a.L + l, m2 = 2 * a.L + l;
     OuterArgs oa{};
     oa.A[0] = a.dq_T;
     oa.B[0] = a.x_in[l];
@@ -818,15 +899,14 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
     oa.A[1] = a.du_T;
     oa.B[1] = a.x_in[l];
     oa.C[1] = a.dW2[l];
-    const int slot = a.L + 2 * l;  // ntiles2 == ntiles (256 x 256 tiles of d x d_ff or d_ff x d)
-    FPO_LAUNCH("outer", st,
-               launch_outer<TileBF16>(dim3(ntiles2 * 2), st, oa, (int)a.d_ff, (int)a.d, (int)a.T, a.Tp, a.d,
-                                      a.scale, tpart(slot)));
+    const int slot = a.L + 2 * l;  // as many tiles as W3 (256 x 256 tiles of d x d_ff or d_ff x d)
+    const int nbig = launch_outer<TileBF16>(0, 2, 2, st, oa, (int)a.d_ff, (int)a.d, (int)a.T, a.Tp, a.d, a.scale, tpart(slot));
     FPO_CHECK_LAUNCH();
     if ((e = handoff()) != hipSuccess) return e;
     const bool last = l + 1 == a.L;
-    if ((e = release(m1, slot, ntiles2, false, last)) != hipSuccess) return e;
-    if ((e = release(m2, slot + 1, ntiles2, false, last)) != hipSuccess) return e;
+    if ((e = reduce(2, slot, nbig, a.L + l, a.L, false)) != hipSuccess) return e;
+    if ((e = update(a.L + l, last)) != hipSuccess) return e;
+    if ((e = update(2 * a.L + l, last)) != hipSuccess) return e;
   }
   if ((e = hipEventRecord(done, side)) != hipSuccess) return e;
   if ((e = hipStreamWaitEvent(st, done, 0)) != hipSuccess) return e;

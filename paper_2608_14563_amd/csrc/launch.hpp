@@ -20,6 +20,42 @@ inline void chunk_span(int64_t V, int nchunk, int64_t cw, int64_t cq, int nwide,
   *w = c == nchunk - 1 ? V - *v0 : cw + (c < nwide ? cq : 0);
 }
 
+inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+constexpr int64_t kCus = 256;  // compute units: one 256 x 256 or 128 x 128 bf16 tile each
+
+// How a bf16 launch of `mats` M x N products over K is cut: its 256 x 256 tiles
+// [0, nbig) as such, the others as 128 x 128 quarters (split_tile), by the least
+// estimated time. A wave of 256 tiles takes 1.6 us per 64-deep K tile when it is
+// full, towards 1.0 when few CUs compete for memory, and 14 us around the K loop;
+// a wave of quarters 0.55 us and 7.5 us (measured over K = 256 .. 4096 with 64 to
+// 256 tiles and 256 to 768 quarters: 64 tiles over K = 256 / 1024 / 4096 take 18 / 30
+// / 79 us, as 256 quarters 11 / 16 / 40 us; 192 tiles 20 / 37 / 117 us, 24 / 46 / 141
+// us as quarters). So the last wave goes over when it is a quarter full or less, a
+// launch of at most 64 tiles altogether, and a ragged one whose big tiles are
+// mostly padding.
+// The quarters' copies run up to four K tiles past the end in 32-bit offsets: rows
+// longer than 2^21 entries (ld: of the N-contiguous B operand) keep the big tiles.
+struct TileSplit {
+  int64_t nbig;
+  double us;
+};
+inline TileSplit big_tiles(int64_t M, int64_t N, int64_t K, int64_t mats, int64_t ld = 0) {
+  const int64_t n = ceil_div(M, 256) * ceil_div(N, 256) * mats, rem = n % kCus, whole = n - rem;
+  const double kt = (double)ceil_div(K, 64);
+  auto big = [&](int64_t tiles) { return tiles ? (1.0 + 0.6 * (double)tiles / kCus) * kt + 14.0 : 0.0; };
+  auto quarters = [&](int64_t q) { return (double)ceil_div(q, kCus) * (0.55 * kt + 7.5); };
+  const double waves = (double)(n / kCus) * big(kCus);
+  TileSplit best{n, waves + big(rem)};
+  if (ld > ((int64_t)1 << 21)) return best;
+  // quarters move more data for the same work: only where they are clearly faster
+  const double part = quarters(4 * rem) + 2.0;  // one more launch
+  if (whole && part < 0.85 * big(rem)) best = TileSplit{whole, waves + part};
+  const double all = quarters(ceil_div(M, 128) * ceil_div(N, 128) * mats);
+  if (all < 0.85 * best.us) best = TileSplit{0, all};
+  return best;
+}
+
 struct OeLaunch {
   bool bf16;
   int64_t T, d, V, Vc;  // Vc: widest chunk, rounded up to 256
@@ -27,7 +63,6 @@ struct OeLaunch {
   int nchunk, nwide;    // chunk layout (chunk_span)
   int64_t cw, cq;
   int nsplit;
-  int tile;             // edge of the GEMM tiles: 256 (bf16) or 64 (fp32)
   float eps, min_rms;
   const void* h_final;
   const void* gamma;
@@ -63,7 +98,7 @@ struct PgLaunch {
   bool full_mlp;
   int64_t T, d, d_ff, Tp;
   int L;
-  int tile;                         // edge of the GEMM tiles, as in OeLaunch
+  int tile;                         // edge of the GEMM tiles: 256 (bf16; see big_tiles) or 64 (fp32)
   float scale;
   const void* g_lp;                 // [T, d]
   const void* a[kMaxMats];          // [T, d_ff]

@@ -90,6 +90,18 @@ def test_fp32_tile_edges(dev, T, d, V):
     check_against_oracle(x, g, W, y, "f32", got)
 
 
+@pytest.mark.parametrize("T,d,V", [(128, 64, 128), (1, 8, 136), (127, 72, 1000), (129, 200, 264), (300, 328, 4104),
+                                   (384, 512, 640), (256, 64, 65800)])
+def test_bf16_quarter_tiles(dev, T, d, V):
+    """128 x 128 quarters: fewer K tiles than ring stages and more, whole and
+    partial, a row or column either side of a tile, tokens or entries that leave
+    quarters of a 256 x 256 tile empty; (256, 64, 65800) has 256 big tiles and two
+    left over as quarters, the last partly outside."""
+    c, x, g, W, y = small_case(I.CONFIGS[1], T, d, V)
+    got = run_gpu(x, g, W, y, "bf16", dev)
+    check_against_oracle(x, g, W, y, "bf16", got)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_more_tokens_than_a_second_grid_dimension_holds(dev, dtype):
     """T = 65600, above the 65536 cap of a second grid dimension: the

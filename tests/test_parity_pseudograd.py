@@ -44,11 +44,16 @@ def run_w3(c, g, acts, dev, refs=None, store=True):
 # fp32 64 x 64 x 32 tiles: one to four K tiles, whole and partial, a row or column either side of a tile
 F32_EDGES = [(0, 1, 64, 64, 1), (0, 32, 72, 56, 2), (0, 33, 64, 136, 1), (0, 64, 56, 72, 3), (0, 97, 128, 64, 1)]
 
+# bf16 128 x 128 quarters: one to six K tiles, a row or column either side of a tile; the last
+# list has 256 big tiles and 8 left over as quarters
+QUARTERS = [(1, 5, 128, 128, 1), (1, 64, 136, 120, 2), (1, 130, 8, 264, 1), (1, 333, 384, 640, 1),
+            (1, 72, 2048, 2816, 3)]
+
 
 # (1, 256, 256, 512, 2) and (1, 512, 512, 768, 3): whole tiles (copy form without bounds)
 @pytest.mark.parametrize("cid,T,d,d_ff,L", [(0, 128, 256, 688, 2), (0, 300, 264, 520, 3), (1, 300, 264, 520, 2),
                                             (1, 1000, 512, 1032, 2), (1, 1, 256, 512, 1), (3, 333, 256, 1000, 2),
-                                            (1, 256, 256, 512, 2), (1, 512, 512, 768, 3)] + F32_EDGES)
+                                            (1, 256, 256, 512, 2), (1, 512, 512, 768, 3)] + F32_EDGES + QUARTERS)
 def test_w3_outer_products(dev, cid, T, d, d_ff, L):
     c = I.CONFIGS[cid].shrink(T=T, d=d, d_ff=d_ff, L=L)
     g = signal(c)
@@ -90,7 +95,9 @@ def test_fused_diagnostic_cosine(dev, cid):
         assert np.array_equal(with_store["dot"], fused["dot"])
 
 
-@pytest.mark.parametrize("cid,T,d,d_ff,L", [(0, 128, 256, 688, 2), (1, 200, 256, 520, 2), (1, 256, 256, 512, 2)])
+# (1, 1024, 64, 16640, 1): the error GEMM has 256 big tiles and four left over as quarters
+@pytest.mark.parametrize("cid,T,d,d_ff,L", [(0, 128, 256, 688, 2), (1, 200, 256, 520, 2), (1, 256, 256, 512, 2),
+                                            (1, 130, 72, 136, 1), (1, 1024, 64, 16640, 1)])
 def test_full_mlp(dev, cid, T, d, d_ff, L):
     c = I.CONFIGS[cid].shrink(T=T, d=d, d_ff=d_ff, L=L)
     g = signal(c)
