@@ -804,12 +804,12 @@ static hipError_t pg_overlap_init(PgOverlap& p, int dev) {
 // beside an outer-product GEMM's on the same CUs) stream on a side stream while
 // the following launches run, with one workgroup per CU so that each CU holds
 // one GEMM workgroup and one update workgroup; the updates released by the last
-// launch have the machine to itself. With the full MLP, the W3 launches come
-// first, then per layer the W1/W2 signal GEMM (eq. errh: all registers, so an
-// update workgroup and an errh workgroup take turns on a CU) and one launch of
-// both W1/W2 outer products, which releases both updates. Same per-block arithmetic and reduction order as the
-// separate calls, so results are bit-identical to them. The side stream and its
-// two events are the caller's (ov) or, when ov is null, the device's
+// launch have the machine to itself. With the full MLP, each layer's W1/W2 signal
+// GEMM (eq. errh) and one launch of both its W1/W2 outer products, which releases
+// both updates, come first and the W3 launches last, so that one update and not two
+// runs alone at the end (Falcon3 shapes, two layers, AdamW: 6.13 -> 5.98 ms). Same
+// per-block arithmetic and reduction order as the separate calls, so results are
+// bit-identical to them. The side stream and its two events are the caller's (ov) or, when ov is null, the device's
 // library-owned set, whose enqueue sequence is serialised by a lock.
 static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, hipStream_t side,
                                             hipEvent_t ready_l, hipEvent_t done, int cus);
@@ -869,22 +869,6 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
     if ((r = hipEventRecord(ready_l, st)) != hipSuccess) return r;
     return hipStreamWaitEvent(side, ready_l, 0);
   };
-  for (int l = 0; l < a.L; ++l) {
-    OuterArgs oa{};
-    oa.A[0] = signal_T<uint16_t>(a, l);
-    oa.B[0] = a.a[l];
-    oa.C[0] = a.dW3[l];
-    oa.Cb[0] = a.dW3_bf16[l];
-    oa.R[0] = a.ref[l];
-    const int nbig = launch_outer<TileBF16>(l, 1, a.L, st, oa, (int)a.d, (int)a.d_ff, (int)a.T, a.Tp, a.d_ff, a.scale,
-                                            tpart(l));
-    FPO_CHECK_LAUNCH();
-    // layer l's tiles are complete: its norm reduction and update follow on the
-    // side stream, so the next layer's outer products start right away
-    if ((e = handoff()) != hipSuccess) return e;
-    if ((e = reduce(1, l, nbig, l, 1, true)) != hipSuccess) return e;
-    if ((e = update(l, !a.full_mlp && l + 1 == a.L)) != hipSuccess) return e;
-  }
   // full MLP: W1/W2 signals through W3_init (eq. errh), then both outer
   // products of the layer in one launch, their updates released together
   for (int l = 0; a.full_mlp && l < a.L; ++l) {
@@ -903,10 +887,25 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
     const int nbig = launch_outer<TileBF16>(0, 2, 2, st, oa, (int)a.d_ff, (int)a.d, (int)a.T, a.Tp, a.d, a.scale, tpart(slot));
     FPO_CHECK_LAUNCH();
     if ((e = handoff()) != hipSuccess) return e;
-    const bool last = l + 1 == a.L;
     if ((e = reduce(2, slot, nbig, a.L + l, a.L, false)) != hipSuccess) return e;
-    if ((e = update(a.L + l, last)) != hipSuccess) return e;
-    if ((e = update(2 * a.L + l, last)) != hipSuccess) return e;
+    if ((e = update(a.L + l, false)) != hipSuccess) return e;
+    if ((e = update(2 * a.L + l, false)) != hipSuccess) return e;
+  }
+  for (int l = 0; l < a.L; ++l) {
+    OuterArgs oa{};
+    oa.A[0] = signal_T<uint16_t>(a, l);
+    oa.B[0] = a.a[l];
+    oa.C[0] = a.dW3[l];
+    oa.Cb[0] = a.dW3_bf16[l];
+    oa.R[0] = a.ref[l];
+    const int nbig = launch_outer<TileBF16>(l, 1, a.L, st, oa, (int)a.d, (int)a.d_ff, (int)a.T, a.Tp, a.d_ff, a.scale,
+                                            tpart(l));
+    FPO_CHECK_LAUNCH();
+    // layer l's tiles are complete: its norm reduction and update follow on the
+    // side stream, so the next layer's outer products start right away
+    if ((e = handoff()) != hipSuccess) return e;
+    if ((e = reduce(1, l, nbig, l, 1, true)) != hipSuccess) return e;
+    if ((e = update(l, l + 1 == a.L)) != hipSuccess) return e;
   }
   if ((e = hipEventRecord(done, side)) != hipSuccess) return e;
   if ((e = hipStreamWaitEvent(st, done, 0)) != hipSuccess) return e;
