@@ -456,7 +456,11 @@ __device__ __forceinline__ void errh_epilogue2(const f32x16 (&acc)[FM][FN], cons
 // du^T are stored. (Stored directly, each lane's 8-byte runs of 4 tokens land
 // Tp apart: about 60 us of a 170 us tile at the OLMo-2 shapes; ragged tiles
 // still take that form.) q and u are read as 8-byte runs of the lane's 4
-// columns, one fragment group ahead of their use.
+// columns, kAhead fragment groups ahead of their use (1 to 4: within 1%).
+// The kernel stays at 344 registers so that an update workgroup (116 to 140) fits
+// beside it: with 64-bit addresses for every row it took all 512, the two took
+// turns on a CU, and a Falcon3-shaped full-MLP AdamW step of two layers took 5.97 ms
+// instead of 5.85 (errh alone is as fast: 0.67 ms a layer).
 __device__ __forceinline__ void errh_epilogue_lds(f32x16 (&acc)[4][4], G2Smem& sm, int m0, int n0,
                                                   const uint16_t* __restrict__ q,
                                                   const uint16_t* __restrict__ u, int Tp,
@@ -464,10 +468,15 @@ __device__ __forceinline__ void errh_epilogue_lds(f32x16 (&acc)[4][4], G2Smem& s
                                                   uint16_t* __restrict__ du_T) {
   const AccMap2<true> mp;
   const int jl0 = mp.col(0);  // tile-relative first of the lane's 4 columns
-  const int j0 = n0 + jl0;
   const int tr0 = mp.row(0, 0);  // tile-relative first token of the lane
-  const int64_t lane_off = (int64_t)(m0 + tr0) * d_ff + j0;  // element (token m0 + tr0, column j0)
+  // buffer loads: the lane's offset in one register, the row's in the scalar
+  // offset (T d_ff <= 2^30 and 256 rows a tile: both below 2^31)
+  const int64_t tile0 = (int64_t)m0 * d_ff + n0;
+  const auto rq = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(q) + tile0, 0, 0x7fffffff, 0x00020000);
+  const auto ru = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(u) + tile0, 0, 0x7fffffff, 0x00020000);
+  const int lane_off = (tr0 * d_ff + jl0) * 2;
   char* lds = reinterpret_cast<char*>(sm.s);
+  constexpr int kAhead = 2;  // groups of loads in flight
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
     // group k = 4 f + g: tokens m0 + tr0 + 32 f + 8 g .. + 3 (a uniform step from the lane's first)
@@ -475,23 +484,26 @@ __device__ __forceinline__ void errh_epilogue_lds(f32x16 (&acc)[4][4], G2Smem& s
       const int dt = 32 * (k >> 2) + 8 * (k & 3);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t o = lane_off + (int64_t)(dt + r) * d_ff;
-        qv[r] = *reinterpret_cast<const u32x2*>(q + o);
-        uv[r] = pass == 0 ? *reinterpret_cast<const u32x2*>(u + o) : u32x2{0u, 0u};
+        const int o = (dt + r) * d_ff * 2;
+        qv[r] = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(rq, lane_off, o, 0));
+        uv[r] = pass == 0 ? __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(ru, lane_off, o, 0))
+                          : u32x2{0u, 0u};
       }
     };
-    u32x2 qn[4], un[4];
-    load(0, qn, un);
+    u32x2 qn[kAhead][4], un[kAhead][4];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) load(k, qn[k], un[k]);
 #pragma unroll
     for (int k = 0; k < 16; ++k) {
       const int f = k >> 2, g = k & 3;
       u32x2 qv[4], uv[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        qv[r] = qn[r];
-        uv[r] = un[r];
+        qv[r] = qn[k % kAhead][r];
+        uv[r] = un[k % kAhead][r];
       }
-      if (k + 1 < 16) load(k + 1, qn, un);
+      if (k + kAhead < 16) load(k + kAhead, qn[k % kAhead], un[k % kAhead]);
+      __builtin_amdgcn_sched_barrier(0);
       const int tl0 = mp.row(f, 4 * g);  // tile-relative tokens tl0 .. tl0 + 3
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -516,13 +528,12 @@ __device__ __forceinline__ void errh_epilogue_lds(f32x16 (&acc)[4][4], G2Smem& s
       }
     }
     __syncthreads();
-    uint16_t* dst = pass == 0 ? dq_T : du_T;
+    uint16_t* dst = (pass == 0 ? dq_T : du_T) + (int64_t)n0 * Tp + m0;
     const int c = threadIdx.x & 31;
 #pragma unroll 4
     for (int kk = 0; kk < 32; ++kk) {
       const int jl = (int)(threadIdx.x >> 5) + 8 * kk;
-      const int t = m0 + 8 * c;
-      *reinterpret_cast<u32x4*>(dst + (int64_t)(n0 + jl) * Tp + t) =
+      *reinterpret_cast<u32x4*>(dst + (int64_t)jl * Tp + 8 * c) =
             *reinterpret_cast<const u32x4*>(lds + jl * 512 + ((c ^ ((jl >> 2) & 31)) * 16));
     }
     __syncthreads();
