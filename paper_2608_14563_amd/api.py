@@ -38,6 +38,12 @@ def _p(t: Optional[torch.Tensor], dtype: Optional[torch.dtype] = None, shape=Non
     shape (a tuple: exact; an int: at least that many elements)."""
     if t is None:
         return None
+    # the usual case on the fewest attribute reads (a step passes some thirty
+    # tensors; at the smallest sizes the host's share of a call is most of it)
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.is_contiguous() and (dtype is None or t.dtype == dtype)
+            and (dev is None or t.device == dev)
+            and (shape is None or (t.shape == shape if isinstance(shape, tuple) else t.numel() >= shape))):
+        return t.data_ptr()
     if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
         raise ValueError(f"{name}: libfpo takes GPU tensors")
     if dev is not None and t.device != dev:
@@ -74,11 +80,15 @@ class _Keep:
             return None
         if n is not None and len(tensors) != n:
             raise ValueError(f"{name}: {len(tensors)} entries, expected {n}")
-        a = (C.c_void_p * max(1, len(tensors)))()
-        for i, t in enumerate(tensors):
-            a[i] = _p(t, dtype, shape(i) if callable(shape) else shape, dev, f"{name}[{i}]")
+        try:
+            ptrs = [_p(t, dtype, shape(i) if callable(shape) else shape, dev, name) for i, t in enumerate(tensors)]
+        except (TypeError, ValueError):
+            for i, t in enumerate(tensors):  # again, naming the entry
+                _p(t, dtype, shape(i) if callable(shape) else shape, dev, f"{name}[{i}]")
+            raise
+        a = (C.c_void_p * max(1, len(tensors)))(*ptrs)
         self.refs.append(a)
-        return C.cast(a, L.PP)
+        return a  # ctypes passes an array where a pointer to its items is declared
 
     def i64(self, vals):
         a = (C.c_int64 * len(vals))(*vals)
@@ -154,7 +164,6 @@ def _upd_bufs(keep: _Keep, W_master, W_lp, state1, state2, W_sumsq, clip_scale, 
     n = len(numels)
     if W_master is None:
         raise ValueError("W_master is required")
-    sh = lambda m: numels[m]  # noqa: E731
 
     def same(ts, name):
         if ts is not None:
@@ -164,8 +173,8 @@ def _upd_bufs(keep: _Keep, W_master, W_lp, state1, state2, W_sumsq, clip_scale, 
 
     for ts, name in ((W_master, "W_master"), (W_lp, "W_lp"), (state1, "state1"), (state2, "state2")):
         same(ts, name)
-    return L.UpdateBufs(keep.arr(W_master, F32, sh, dev, n, "W_master"), keep.arr(W_lp, lp_dtype, sh, dev, n, "W_lp"),
-                        keep.arr(state1, F32, sh, dev, n, "state1"), keep.arr(state2, F32, sh, dev, n, "state2"),
+    return L.UpdateBufs(keep.arr(W_master, F32, None, dev, n, "W_master"), keep.arr(W_lp, lp_dtype, None, dev, n, "W_lp"),
+                        keep.arr(state1, F32, None, dev, n, "state1"), keep.arr(state2, F32, None, dev, n, "state2"),
                         _p(W_sumsq, F64, n, dev, "W_sumsq"), _p(clip_scale, F32, n, dev, "clip_scale"))
 
 
