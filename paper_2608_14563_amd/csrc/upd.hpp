@@ -182,7 +182,8 @@ __device__ __forceinline__ f32x4 load_grad4(const void* gp, int64_t i) {
 }
 
 // Pass 1 over block b: new optimizer state (written) and the block's
-// ||delta||^2 (to *part_b).
+// ||delta||^2 (to *part_b). W and the state are read again by pass 2, so their
+// accesses are not non-temporal here (the state's loads are: it is rewritten).
 template <bool GB16, bool ADAM>
 __device__ __forceinline__ void delta_block(const void* __restrict__ gp, const float* __restrict__ W,
                                             float* __restrict__ s1, float* __restrict__ s2,
@@ -200,7 +201,7 @@ __device__ __forceinline__ void delta_block(const void* __restrict__ gp, const f
     if (i < end) {
       gv[u] = load_grad4<GB16>(gp, i);
       if constexpr (ADAM) {
-        w[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(W + i));
+        w[u] = *reinterpret_cast<const f32x4*>(W + i);
         v2[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(s2 + i));
       }
       if (!fresh) v1[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(s1 + i));
@@ -224,8 +225,8 @@ __device__ __forceinline__ void delta_block(const void* __restrict__ gp, const f
       const float dl = upd_delta<ADAM>(w[u][e], nb[e], nv[e], o);
       ss += dl * dl;
     }
-    if (s1) __builtin_nontemporal_store(nb, reinterpret_cast<f32x4*>(s1 + i));
-    if constexpr (ADAM) __builtin_nontemporal_store(nv, reinterpret_cast<f32x4*>(s2 + i));
+    if (s1) *reinterpret_cast<f32x4*>(s1 + i) = nb;
+    if constexpr (ADAM) *reinterpret_cast<f32x4*>(s2 + i) = nv;
   }
   const double t = block_sum_d((double)ss, red);
   if (threadIdx.x == 0) *part_b = t;

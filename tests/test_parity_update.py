@@ -177,6 +177,40 @@ def test_clip_edge_cases(dev):
     assert not torch.isnan(W).any()
 
 
+@pytest.mark.parametrize("kind", [L_.FPO_OPT_SGD, L_.FPO_OPT_ADAMW], ids=["sgd", "adamw"])
+def test_clip_update_groups(dev, kind):
+    """Clip-the-update over matrices that make several groups of the two passes
+    (W and state of 400 MB): a group of several, one matrix above the limit, a last
+    ragged one. Bit-identical to a call per matrix."""
+    g = torch.Generator(device=dev).manual_seed(9)
+    rn = lambda m, std: torch.empty(m, device=dev).normal_(0, std, generator=g)  # noqa: E731
+    numel = [20_000_000, 4100, 10_000_000, 60_000_000, 1_000_004]
+    adam = kind == L_.FPO_OPT_ADAMW
+    W, G = [rn(m, 0.02) for m in numel], [rn(m, 1e-3) for m in numel]
+    s1, s2 = [rn(m, 1e-3) for m in numel], [rn(m, 1e-3).square_() for m in numel] if adam else None
+    ss = torch.stack([(x.double() ** 2).sum() for x in G])
+    Wsq = torch.stack([(x.double() ** 2).sum() for x in W])
+
+    def bufs():
+        c = lambda ts: [x.clone() for x in ts]  # noqa: E731
+        return dict(W=c(W), s1=c(s1), s2=c(s2) if adam else None, lp=[torch.empty_like(x, dtype=torch.bfloat16) for x in W],
+                    Wsq=Wsq.clone(), cs=torch.zeros(len(W), device=dev))
+
+    opt = api.OptConfig(kind=kind, lr=0.5, clip_frac=0.01, step=3, clip_target=L_.FPO_CLIP_UPDATE)
+    a, b = bufs(), bufs()
+    api.fpo_apply_update(opt, G, ss, a["W"], a["s1"], a["Wsq"], W_lp=a["lp"], state2=a["s2"], clip_scale=a["cs"])
+    for m in range(len(W)):
+        i = slice(m, m + 1)
+        api.fpo_apply_update(opt, G[i], ss[i], b["W"][i], b["s1"][i], b["Wsq"][i], W_lp=b["lp"][i],
+                             state2=b["s2"][i] if adam else None, clip_scale=b["cs"][i])
+    torch.cuda.synchronize()
+    assert float(a["cs"].max()) < 1.0  # the clip is active
+    for k in ("W", "s1", "s2", "lp"):
+        for x, y in zip(a[k] or [], b[k] or []):
+            assert torch.equal(x, y), k
+    assert torch.equal(a["Wsq"], b["Wsq"]) and torch.equal(a["cs"], b["cs"])
+
+
 @pytest.mark.parametrize("bdtype", ["f32", "bf16"])
 def test_cosine_shared_signal(dev, bdtype):
     """Runs of pairs that share A (and its length) are streamed together: groups
