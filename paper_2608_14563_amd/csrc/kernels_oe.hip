@@ -23,9 +23,15 @@
 namespace fpo {
 
 // ------------------------------------------------------------------ forward
-// Per-token row kernels (one 256-lane workgroup per token, 1024 entries per
-// sweep) hold rows of up to this many sweeps in registers between passes.
-constexpr int kRowRegIters = 8;
+// Per-token row kernels (one workgroup of NT lanes per token, 4 NT entries per
+// sweep) hold rows of up to kRowRegs entries in registers between passes. NT is
+// 1024 where there are few tokens for the chip's CUs and long rows (row_lanes):
+// with 256 lanes a row's loads are a few long chains, and one or two workgroups
+// do not fill a CU. d = 4096, finalize_vjp, 256 / 1024 lanes: T = 64 16 / 7 us, 128 20 /
+// 10, 512 25 / 19, 1024 13 / 15 (two splits), 2048 28 / 29; rms_forward 4.9 / 4.0 at 64,
+// 8.3 / 7.6 at 512, 9 / 10.5 at 1024; d = 1024, T = 300 5.5 / 6.0.
+constexpr int kRowRegs = 8192;
+static int row_lanes(int64_t T, int64_t d) { return T <= 2 * kCus && d >= 2048 ? 1024 : 256; }
 
 // The value of f after rounding to the storage type T.
 template <typename T> __device__ __forceinline__ float round_to(float f);
@@ -37,8 +43,8 @@ template <> __device__ __forceinline__ float round_to<uint16_t>(float f) { retur
 // with v the token's target (entry 0 for a target outside [0, V)) from the
 // stored (rounded) y: any logit is at most the row maximum, which is all the
 // staging of p~ = exp(z - R) needs (see logits_epilogue).
-template <typename T>
-__global__ __launch_bounds__(256) void rms_forward_kernel(const T* __restrict__ x,
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void rms_forward_kernel(const T* __restrict__ x,
                                                           const T* __restrict__ gamma, int d,
                                                           float eps, T* __restrict__ y,
                                                           const T* __restrict__ W_U,
@@ -49,16 +55,17 @@ __global__ __launch_bounds__(256) void rms_forward_kernel(const T* __restrict__ 
   __shared__ float red[16];
   const int64_t row = blockIdx.x;
   const T* xr = x + row * d;
-  // rows of up to kRowRegIters * 1024 entries are read once (held in registers)
+  constexpr int kSweep = 4 * NT, kRowRegIters = kRowRegs / kSweep;
+  // rows of up to kRowRegs entries are read once (held in registers)
   float ss = 0.f;
   f32x4 xk[kRowRegIters];
 #pragma unroll
   for (int it = 0; it < kRowRegIters; ++it) {
-    const int k = threadIdx.x * 4 + it * 1024;
+    const int k = threadIdx.x * 4 + it * kSweep;
     xk[it] = k < d ? ld4(xr, k) : f32x4{0.f, 0.f, 0.f, 0.f};
     ss += xk[it].x * xk[it].x + xk[it].y * xk[it].y + xk[it].z * xk[it].z + xk[it].w * xk[it].w;
   }
-  for (int k = threadIdx.x * 4 + kRowRegIters * 1024; k < d; k += 1024) {
+  for (int k = threadIdx.x * 4 + kRowRegs; k < d; k += kSweep) {
     const f32x4 v = ld4(xr, k);
     ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
   }
@@ -76,10 +83,10 @@ __global__ __launch_bounds__(256) void rms_forward_kernel(const T* __restrict__ 
   };
 #pragma unroll
   for (int it = 0; it < kRowRegIters; ++it) {
-    const int k = threadIdx.x * 4 + it * 1024;
+    const int k = threadIdx.x * 4 + it * kSweep;
     if (k < d) out(k, xk[it]);
   }
-  for (int k = threadIdx.x * 4 + kRowRegIters * 1024; k < d; k += 1024) out(k, ld4(xr, k));
+  for (int k = threadIdx.x * 4 + kRowRegs; k < d; k += kSweep) out(k, ld4(xr, k));
   zr = block_sum(zr, red);
   if (threadIdx.x == 0) {
     ref[row] = zr;
@@ -571,8 +578,8 @@ __global__ __launch_bounds__(256, 1) void proj_chunk_kernel(
 // The loss takes the target logit that rms_forward formed from the stored y
 // (the same products and summation order as a second pass here would use),
 // so the row of y is not read again.
-template <typename T>
-__global__ __launch_bounds__(256) void finalize_vjp_kernel(
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void finalize_vjp_kernel(
     int d, int V, int nsplit, int64_t split_stride, const float* __restrict__ G,
     const float* __restrict__ runM, const float* __restrict__ runS,
     const int32_t* __restrict__ runA, const float* __restrict__ zt,
@@ -580,6 +587,7 @@ __global__ __launch_bounds__(256) void finalize_vjp_kernel(
     const T* __restrict__ gamma, float eps, float min_rms, float* __restrict__ g_tilde,
     T* __restrict__ g_tilde_lp, float* __restrict__ g_pre, float* __restrict__ lse,
     float* __restrict__ loss, int32_t* __restrict__ argmax, int32_t* __restrict__ bad) {
+  constexpr int kSweep = 4 * NT, kRowRegIters = kRowRegs / kSweep;
   __shared__ float red[32];
   const int64_t row = blockIdx.x;
   const int tg = targets[row];
@@ -590,7 +598,7 @@ __global__ __launch_bounds__(256) void finalize_vjp_kernel(
   float* gt = g_tilde + row * d;
   float ss = 0.f, cd = 0.f;
   // pass 1: g = sum_s G_s / S - W_U[y] and the row reductions. Rows of up to
-  // kRowRegIters * 1024 entries keep g and x in registers for pass 2; longer
+  // kRowRegs entries keep g and x in registers for pass 2; longer
   // rows park the rest of g in the g~ row (rewritten in pass 2).
   f32x4 gk[kRowRegIters], xk[kRowRegIters];
   auto pass1 = [&](int k) -> f32x4 {
@@ -607,7 +615,7 @@ __global__ __launch_bounds__(256) void finalize_vjp_kernel(
   };
 #pragma unroll
   for (int it = 0; it < kRowRegIters; ++it) {
-    const int k = threadIdx.x * 4 + it * 1024;
+    const int k = threadIdx.x * 4 + it * kSweep;
     gk[it] = xk[it] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (k < d) {
       gk[it] = pass1(k);
@@ -615,7 +623,7 @@ __global__ __launch_bounds__(256) void finalize_vjp_kernel(
       reduce(gk[it], xk[it], ld4(gamma, k));
     }
   }
-  for (int k = threadIdx.x * 4 + kRowRegIters * 1024; k < d; k += 1024) {
+  for (int k = threadIdx.x * 4 + kRowRegs; k < d; k += kSweep) {
     const f32x4 g = pass1(k), xv = ld4(xr, k);
     *reinterpret_cast<f32x4*>(gt + k) = g;
     reduce(g, xv, ld4(gamma, k));
@@ -638,10 +646,10 @@ __global__ __launch_bounds__(256) void finalize_vjp_kernel(
   };
 #pragma unroll
   for (int it = 0; it < kRowRegIters; ++it) {
-    const int k = threadIdx.x * 4 + it * 1024;
+    const int k = threadIdx.x * 4 + it * kSweep;
     if (k < d) out(k, gk[it], xk[it]);
   }
-  for (int k = threadIdx.x * 4 + kRowRegIters * 1024; k < d; k += 1024)
+  for (int k = threadIdx.x * 4 + kRowRegs; k < d; k += kSweep)
     out(k, *reinterpret_cast<const f32x4*>(gt + k), ld4(xr, k));
   if (threadIdx.x == 0) {
     const float l_se = runM[row] + logf(S);
@@ -705,9 +713,14 @@ static hipError_t run_output_error(const OeLaunch& a) {
   const T* gamma = (const T*)a.gamma;
   const T* W = (const T*)a.W_U;
   T* P = (T*)a.P;
-  FPO_LAUNCH("rms_forward", st,
-             rms_forward_kernel<T><<<dim3((unsigned)a.T), dim3(256), 0, st>>>(
-      x, gamma, (int)a.d, a.eps, (T*)a.y, W, a.targets, (int)a.V, a.ref, a.zt, a.bad_targets));
+  const int lanes = row_lanes(a.T, a.d);
+  auto rms = [&](auto nt) {
+    FPO_LAUNCH("rms_forward", st,
+               rms_forward_kernel<T, nt><<<dim3((unsigned)a.T), dim3(nt), 0, st>>>(
+        x, gamma, (int)a.d, a.eps, (T*)a.y, W, a.targets, (int)a.V, a.ref, a.zt, a.bad_targets));
+  };
+  if (lanes == 256) rms(std::integral_constant<int, 256>{});
+  else rms(std::integral_constant<int, 1024>{});
   FPO_CHECK_LAUNCH();
   for (int c = 0; c < a.nchunk; ++c) {
     int64_t v0, width;
@@ -746,11 +759,15 @@ static hipError_t run_output_error(const OeLaunch& a) {
       FPO_CHECK_LAUNCH();
     }
   }
-  FPO_LAUNCH("finalize_vjp", st,
-             finalize_vjp_kernel<T><<<dim3((unsigned)a.T), dim3(256), 0, st>>>(
-      (int)a.d, (int)a.V, a.nsplit, a.T * a.d, a.G, a.runM, a.runS, a.runA, a.zt, a.targets, W,
-      x, gamma, a.eps, a.min_rms, a.g_tilde, (T*)a.g_tilde_lp, a.g_pre, a.lse, a.loss, a.argmax,
-      a.bad_targets));
+  auto finalize = [&](auto nt) {
+    FPO_LAUNCH("finalize_vjp", st,
+               finalize_vjp_kernel<T, nt><<<dim3((unsigned)a.T), dim3(nt), 0, st>>>(
+        (int)a.d, (int)a.V, a.nsplit, a.T * a.d, a.G, a.runM, a.runS, a.runA, a.zt, a.targets, W,
+        x, gamma, a.eps, a.min_rms, a.g_tilde, (T*)a.g_tilde_lp, a.g_pre, a.lse, a.loss, a.argmax,
+        a.bad_targets));
+  };
+  if (lanes == 256) finalize(std::integral_constant<int, 256>{});
+  else finalize(std::integral_constant<int, 1024>{});
   FPO_CHECK_LAUNCH();
   return hipSuccess;
 }
