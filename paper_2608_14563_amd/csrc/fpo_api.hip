@@ -687,6 +687,21 @@ int fpo_pseudograd(const fpo_pg_desc* desc, const void* g_tilde_lp, const void* 
     if (e != hipSuccess) return hip_fail(e, "fpo_pseudograd overlapped launch");
     return FPO_OK;
   }
+  // small matrices (at most 256 tile partials each): the update sums their norms
+  // itself, one launch less (fp32, T = 128, 256 x 688 x 2, SGD: 33.9 -> 30.5 us)
+  if (opt && !U.clip_update && !full && !ref) {
+    const int64_t nbig = fpo::pseudograd_w3_nbig(P);
+    int64_t slots = 0;
+    for (int64_t l = 0; l < L; ++l)
+      slots = std::max(slots, fpo::part_slot((l + 1) * pl.ntiles, nbig) - fpo::part_slot(l * pl.ntiles, nbig));
+    if (slots <= 256) {
+      P.defer_norms = true;
+      U.tile_part = P.part;
+      U.ntiles = pl.ntiles;
+      U.nbig = nbig;
+      U.sumsq_out = sumsq;
+    }
+  }
   e = fpo::launch_pseudograd(P);
   if (e != hipSuccess) return hip_fail(e, "fpo_pseudograd launch");
   if (opt) {

@@ -286,10 +286,6 @@ __device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[FM][FN], con
   }
 }
 
-// Partials: tile ids run over (matrix, tile) in dispatch order; big tile g has
-// slot g, the quarters of a later tile four slots each (part_slot).
-__host__ __device__ inline int64_t part_slot(int64_t g, int64_t nbig) { return g < nbig ? g : 4 * g - 3 * nbig; }
-
 template <class E, bool FAST>
 __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, int N, int K,
                                                        int64_t lda, int64_t ldb, float scale,
@@ -753,6 +749,7 @@ static hipError_t run_pseudograd(const PgLaunch& a) {
     }
     const int nbig = launch_outer<E>(0, a.L, a.L, st, oa, (int)a.d, (int)a.d_ff, (int)a.T, a.Tp, a.d_ff, a.scale, a.part);
     FPO_CHECK_LAUNCH();
+    if (a.defer_norms) return hipSuccess;
     FPO_LAUNCH("reduce_parts", st,
                reduce_parts_kernel<<<dim3(a.L), dim3(256), 0, st>>>(a.part, ntiles, nbig, 0, 1, a.sumsq, a.ref_dot,
                                                          a.ref_sumsq, a.ref_cos));
@@ -922,6 +919,11 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
   if ((e = hipStreamWaitEvent(st, done, 0)) != hipSuccess) return e;
   // ||W'||^2 and the clip factors of every matrix
   return launch_update(u, false);
+}
+
+int64_t pseudograd_w3_nbig(const PgLaunch& a) {
+  if (!a.bf16) return pseudograd_tiles(a.tile, a.d, a.d_ff) * a.L;
+  return big_tiles(a.d, a.d_ff, a.T, a.L, a.d_ff).nbig;
 }
 
 hipError_t launch_pseudograd(const PgLaunch& a) {

@@ -31,15 +31,36 @@ __device__ __forceinline__ int find_mat(const int64_t* blk0, int n, int64_t b) {
   return m;
 }
 
+// Where ||dW||^2 comes from: the outer products' tile partials of matrices m0 + m
+// (part_slot) instead of grad_sumsq, when part is set. At small sizes the reduction
+// kernel between the two costs more than every block summing a few hundred
+// partials again (same order, same bits).
+struct NormParts {
+  const double* part;
+  int64_t ntiles, nbig;
+  int m0;
+  double* out;
+};
+
 template <bool GB16, bool ADAM>
 __global__ __launch_bounds__(256) void update_kernel(UpdArgs a, int n, OptScalars o,
                                                      const double* __restrict__ grad_sumsq,
                                                      const double* __restrict__ W_sumsq,
-                                                     double* __restrict__ part) {
+                                                     double* __restrict__ part, NormParts np) {
   __shared__ double red[16];
   const int64_t b = blockIdx.x;
   const int m = find_mat(a.blk0, n, b);
-  const float s = clip_factor(grad_sumsq[m], W_sumsq[m], o.clip_frac);
+  double gs;
+  if (np.part) {
+    const int64_t mg = np.m0 + m, s0 = part_slot(mg * np.ntiles, np.nbig), s1 = part_slot((mg + 1) * np.ntiles, np.nbig);
+    double v = 0.0;
+    for (int64_t t = s0 + threadIdx.x; t < s1; t += 256) v += np.part[3 * t];
+    gs = block_sum_d(v, red);
+    if (threadIdx.x == 0 && b == a.blk0[m]) np.out[m] = gs;
+  } else {
+    gs = grad_sumsq[m];
+  }
+  const float s = clip_factor(gs, W_sumsq[m], o.clip_frac);
   update_visit<GB16, ADAM, 1>(a.grad[m], a.W[m], a.W_lp[m], a.s1[m], a.s2[m], a.numel[m], b - a.blk0[m], 1,
                                a.blk0[m + 1] - a.blk0[m], s, o, red, part + a.blk0[m]);
 }
@@ -123,16 +144,16 @@ __global__ __launch_bounds__(256) void update_reduce_kernel(UpdArgs a, OptScalar
 // gradient dtype and optimizer.
 static hipError_t launch_update_kernel(const UpdArgs& ua, int n, const OptScalars& o, bool gb16, bool adam,
                                        const double* gs, const double* ws, double* pt, unsigned nb,
-                                       hipStream_t st) {
+                                       hipStream_t st, NormParts np = NormParts{}) {
   const dim3 g(nb);
   if (gb16 && adam)
-    FPO_LAUNCH("update", st, update_kernel<true, true><<<g, dim3(256), 0, st>>>(ua, n, o, gs, ws, pt));
+    FPO_LAUNCH("update", st, update_kernel<true, true><<<g, dim3(256), 0, st>>>(ua, n, o, gs, ws, pt, np));
   else if (gb16)
-    FPO_LAUNCH("update", st, update_kernel<true, false><<<g, dim3(256), 0, st>>>(ua, n, o, gs, ws, pt));
+    FPO_LAUNCH("update", st, update_kernel<true, false><<<g, dim3(256), 0, st>>>(ua, n, o, gs, ws, pt, np));
   else if (adam)
-    FPO_LAUNCH("update", st, update_kernel<false, true><<<g, dim3(256), 0, st>>>(ua, n, o, gs, ws, pt));
+    FPO_LAUNCH("update", st, update_kernel<false, true><<<g, dim3(256), 0, st>>>(ua, n, o, gs, ws, pt, np));
   else
-    FPO_LAUNCH("update", st, update_kernel<false, false><<<g, dim3(256), 0, st>>>(ua, n, o, gs, ws, pt));
+    FPO_LAUNCH("update", st, update_kernel<false, false><<<g, dim3(256), 0, st>>>(ua, n, o, gs, ws, pt, np));
   FPO_CHECK_LAUNCH();
   return hipSuccess;
 }
@@ -243,9 +264,10 @@ hipError_t launch_update(const UpdLaunch& a, bool blocks) {
       }
       clip_ref = a.dsq + m0;
     } else if (blocks) {
+      const NormParts np{a.tile_part, a.ntiles, a.nbig, m0, a.tile_part ? a.sumsq_out + m0 : nullptr};
       if (hipError_t e = launch_update_kernel(ua, n, o, a.grad_bf16, a.kind == kOptAdamW,
                                               a.grad_sumsq + m0, a.W_sumsq + m0, a.part + part_off,
-                                              (unsigned)nb, st))
+                                              (unsigned)nb, st, np))
         return e;
     }
     FPO_LAUNCH("update_reduce", st,

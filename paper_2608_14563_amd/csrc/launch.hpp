@@ -133,10 +133,18 @@ struct PgLaunch {
   void* dq_T;                       // [d_ff, Tp] full-MLP gate error (transposed)
   void* du_T;                       // [d_ff, Tp] full-MLP up error (transposed)
   double* part;                     // per-tile partials
+  bool defer_norms;                 // W3 only, no ref: sumsq is left to launch_update (its tile_part)
   void* stream;
 };
 hipError_t launch_pseudograd(const PgLaunch& a);
 int64_t pseudograd_tiles(int tile, int64_t M, int64_t N);
+
+// Tile partials (three doubles each) of a list of matrices: tile ids run over
+// (matrix, tile) in dispatch order; tile g < nbig has slot g, the quarters of a
+// later one four slots each.
+__host__ __device__ inline int64_t part_slot(int64_t g, int64_t nbig) { return g < nbig ? g : 4 * g - 3 * nbig; }
+// The split of launch_pseudograd's W3 outer products (all layers as one list).
+int64_t pseudograd_w3_nbig(const PgLaunch& a);
 
 constexpr int kOptAdamW = 1;  // fpo_opt_kind FPO_OPT_ADAMW
 
@@ -157,6 +165,11 @@ struct UpdLaunch {
   double* W_sumsq;
   float* clip_scale;
   double* part;
+  // when set, ||dW||^2 comes from these tile partials (one-pass update only): every
+  // update block sums its matrix's, the matrix's first one stores it in sumsq_out
+  const double* tile_part;
+  int64_t ntiles, nbig;
+  double* sumsq_out;
   // clip-the-update mode: the clip bounds ||W' - W|| instead of ||dW|| (two
   // passes; dsq: [n] ||delta||^2 scratch)
   bool clip_update;

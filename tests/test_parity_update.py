@@ -297,14 +297,16 @@ def test_cosine(dev, bdtype):
 @pytest.mark.parametrize("kind", ["sgd", "adamw", "sgd-plain"])
 @pytest.mark.parametrize("T,d,d_ff,L,clip,pffn", [(256, 256, 512, 2, 0.01, False), (300, 264, 1000, 3, 0.01, False),
                                                   (200, 512, 768, 3, 1e-5, False), (300, 264, 1000, 3, 0.01, True),
-                                                  (200, 1032, 1288, 3, 0.01, False)])
+                                                  (200, 1032, 1288, 3, 0.01, False),
+                                                  (64, 64, 136, 40, 1e-3, False)])
 def test_fused_update_matches_separate_calls(dev, kind, T, d, d_ff, L, clip, pffn, target):
     """The W3 pseudogradient with the optimizer fused (bf16: one launch per
     layer carrying that layer's outer products and the previous layer's update)
     is bit-identical to the pseudogradient followed by fpo_apply_update, over two
     steps (momentum / moments carried), including a ragged shape, an active
-    clip (clip_frac 1e-5), and matrices of more update blocks than the GPU has
-    compute units (the overlapped update then visits its blocks grid-stride)."""
+    clip (clip_frac 1e-5), matrices of more update blocks than the GPU has
+    compute units (the overlapped update then visits its blocks grid-stride), and
+    more layers than one update launch takes."""
     c = I.CONFIGS[1].shrink(T=T, d=d, d_ff=d_ff, L=L)
     g = dev_tensor(I.synthetic_signal(c), dev)
     kw = {}
