@@ -223,7 +223,7 @@ __device__ __forceinline__ void outer_epilogue(VA (&acc)[FM][FN], const Map& mp,
 __device__ __forceinline__ float dot(f32x4 a, f32x4 b) { return a.x * b.x + a.y * b.y + a.z * b.z + a.w * b.w; }
 __device__ __forceinline__ float dot(float a, float b) { return a * b; }
 
-template <class Map, int FM, int FN>
+template <bool REF, int OUT, class Map, int FM, int FN>
 __device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[FM][FN], const Map& mp, int m0, int n0, int M,
                                                 int N, float scale, float* __restrict__ C,
                                                 uint16_t* __restrict__ Cb,
@@ -239,7 +239,7 @@ __device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[FM][FN], con
 #pragma unroll
     for (int f = 0; f < FM; ++f) {
       fvec q[16];
-      if (R) {
+      if constexpr (REF) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int row = m0 + mp.row(f, r);
@@ -252,7 +252,7 @@ __device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[FM][FN], con
         const int row = m0 + mp.row(f, r);
         if (!cok || row >= M) continue;
         fvec v = acc_vec<VEC>(acc[f], i, r) * scale;
-        if (Cb) {
+        if constexpr (OUT == 2) {
           if constexpr (VEC == 4) {
             const u32x2 h = {pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w)};
             *reinterpret_cast<u32x2*>(Cb + (int64_t)row * N + c) = h;
@@ -263,9 +263,9 @@ __device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[FM][FN], con
             v = bf16_to_f32(h);
           }
         }
-        if (C) *reinterpret_cast<fvec*>(C + (int64_t)row * N + c) = v;
+        if constexpr (OUT == 1) *reinterpret_cast<fvec*>(C + (int64_t)row * N + c) = v;
         ss += dot(v, v);
-        if (R) {
+        if constexpr (REF) {
           dt += dot(v, q[r]);
           rr += dot(q[r], q[r]);
         }
@@ -286,7 +286,11 @@ __device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[FM][FN], con
   }
 }
 
-template <class E, bool FAST>
+// bf16 kernels: REF: reduced against reference gradients too; OUT: what is stored
+// (0 nothing, 1 fp32 C, 2 bf16 Cb). Decided at run time these were branches in every
+// row of the epilogue: T = 2048, 4096 x 11008 x 4 720 us, 748 with them; T = 512, 2048 x
+// 8192 x 4 115, 124; against references 706, 736; one 4096 x 11008 layer to bf16 169, 180.
+template <class E, bool FAST, bool REF, int OUT>
 __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, int N, int K,
                                                        int64_t lda, int64_t ldb, float scale,
                                                        double* __restrict__ part, int nbig) {
@@ -327,7 +331,7 @@ __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, in
     const Operand A{Am + (int64_t)m0 * lda, lda, band_bytes(M - m0, lda)};
     const Operand B{Bm + n0, ldb, band_bytes(K, ldb, n0)};
     gemm2s_mainloop<true>(sm, acc, A, B, M - m0, N - n0, K, 0, (K + G2S::BK - 1) / G2S::BK);
-    outer_epilogue2(acc, AccMap2S<true>(), m0, n0, M, N, scale, args.C[mat], args.Cb[mat], args.R[mat], red, po);
+    outer_epilogue2<REF, OUT>(acc, AccMap2S<true>(), m0, n0, M, N, scale, args.C[mat], args.Cb[mat], args.R[mat], red, po);
   } else if constexpr (E::EPC == 8) {
     __shared__ G2Smem sm;
     f32x16 acc[4][4];
@@ -335,7 +339,7 @@ __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, in
     const Operand A{Am + (int64_t)m0 * lda, lda, band_bytes(M - m0, lda)};
     const Operand B{Bm + n0, ldb, band_bytes(K, ldb, n0)};
     gemm2_mainloop<true, FAST>(sm, acc, A, B, M - m0, N - n0, K, 0, (K + G2::BK - 1) / G2::BK);
-    outer_epilogue2(acc, AccMap2<true>(), m0, n0, M, N, scale, args.C[mat], args.Cb[mat], args.R[mat], red, po);
+    outer_epilogue2<REF, OUT>(acc, AccMap2<true>(), m0, n0, M, N, scale, args.C[mat], args.Cb[mat], args.R[mat], red, po);
   } else {
     __shared__ GemmSmem<E> sm;
     f32x4 acc[E::FM][E::FN];
@@ -690,18 +694,29 @@ static int launch_outer(int m0, int mats, int of, hipStream_t st, const OuterArg
   int nbig = n;
   if constexpr (E::EPC == 8)
     nbig = (int)std::max<int64_t>(0, std::min<int64_t>(n, big_tiles(M, N, K, of, ldb).nbig - (int64_t)m0 * nt));
-  if (nbig) {
-    if (whole_tiles(M, N, K))
-      FPO_LAUNCH("outer", st, outer_kernel<E, true><<<dim3(nbig), dim3(256), 0, st>>>(
-          oa, M, N, K, lda, ldb, scale, part, nbig));
-    else
-      FPO_LAUNCH("outer", st, outer_kernel<E, false><<<dim3(nbig), dim3(256), 0, st>>>(
-          oa, M, N, K, lda, ldb, scale, part, nbig));
-  }
+  auto launch = [&](auto tile, auto fast, auto with_ref, auto out, int grid) {
+    using TE = decltype(tile);
+    FPO_LAUNCH("outer", st, outer_kernel<TE, fast, with_ref, out><<<dim3(grid), dim3(256), 0, st>>>(
+        oa, M, N, K, lda, ldb, scale, part, nbig));
+  };
+  std::true_type yes;
+  std::false_type no;
+  std::integral_constant<int, 0> none;
+  std::integral_constant<int, 1> f32;
+  std::integral_constant<int, 2> bf16;
   if constexpr (E::EPC == 8) {
-    if (nbig < n)
-      FPO_LAUNCH("outer", st, outer_kernel<TileBF16S, false><<<dim3(4 * (n - nbig)), dim3(256), 0, st>>>(
-          oa, M, N, K, lda, ldb, scale, part, nbig));
+    auto split = [&](auto with_ref, auto out) {
+      if (nbig) {
+        if (whole_tiles(M, N, K)) launch(E{}, yes, with_ref, out, nbig);
+        else launch(E{}, no, with_ref, out, nbig);
+      }
+      if (nbig < n) launch(TileBF16S{}, no, with_ref, out, 4 * (n - nbig));
+    };
+    // the same for all matrices of a launch
+    if (oa.R[0]) oa.Cb[0] ? split(yes, bf16) : oa.C[0] ? split(yes, f32) : split(yes, none);
+    else oa.Cb[0] ? split(no, bf16) : split(no, f32);
+  } else {
+    launch(E{}, no, no, f32, n);  // the fp32 kernel looks at R and C itself
   }
   return nbig;
 }
