@@ -160,8 +160,10 @@ static hipError_t launch_update_kernel(const UpdArgs& ua, int n, const OptScalar
 
 // The update blocks of matrix m alone (no reduction), on stream st; its
 // partials start at part + blk_base, as in launch_update. grid > 0: that many
-// workgroups visit the blocks grid-stride (update_loop_kernel).
-hipError_t launch_update_blocks(const UpdLaunch& a, int m, int64_t blk_base, void* stream, int grid) {
+// workgroups (two_per_cu: twice as many smaller ones, SGD) visit the blocks
+// grid-stride (update_loop_kernel).
+hipError_t launch_update_blocks(const UpdLaunch& a, int m, int64_t blk_base, void* stream, int grid,
+                                bool two_per_cu) {
   hipStream_t st = (hipStream_t)stream;
   const OptScalars o = make_opt_scalars(a);
   UpdArgs ua{};
@@ -179,13 +181,18 @@ hipError_t launch_update_blocks(const UpdLaunch& a, int m, int64_t blk_base, voi
   double* pt = a.part + blk_base;
   const bool adam = a.kind == kOptAdamW;
   if (loop) {
-    // SGD: two blocks per visit (128 VGPRs, still beside an outer-product
-    // workgroup); AdamW's second moment leaves room for one
+    // one workgroup per CU: SGD two blocks per visit (124 or 140 VGPRs beside a
+    // GEMM workgroup's 328 to 344 of 512), AdamW's second moment leaves room for one.
+    // Two per CU (SGD): one block per visit, 76 VGPRs each.
     const dim3 g((unsigned)grid);
     if (adam && a.grad_bf16)
       FPO_LAUNCH("update", st, update_loop_kernel<true, true, 1><<<g, dim3(256), 0, st>>>(ua, o, gs, ws, pt));
     else if (adam)
       FPO_LAUNCH("update", st, update_loop_kernel<false, true, 1><<<g, dim3(256), 0, st>>>(ua, o, gs, ws, pt));
+    else if (a.grad_bf16 && two_per_cu)
+      FPO_LAUNCH("update", st, update_loop_kernel<true, false, 1><<<dim3(2 * g.x), dim3(256), 0, st>>>(ua, o, gs, ws, pt));
+    else if (two_per_cu)
+      FPO_LAUNCH("update", st, update_loop_kernel<false, false, 1><<<dim3(2 * g.x), dim3(256), 0, st>>>(ua, o, gs, ws, pt));
     else if (a.grad_bf16)
       FPO_LAUNCH("update", st, update_loop_kernel<true, false, 2><<<g, dim3(256), 0, st>>>(ua, o, gs, ws, pt));
     else

@@ -180,8 +180,10 @@ struct UpdLaunch {
 // blocks already applied (by the fused pseudogradient launch).
 hipError_t launch_update(const UpdLaunch& a, bool blocks = true);
 // The update blocks of matrix m of `a` on `stream` (partials at part + blk_base);
-// grid > 0: that many workgroups visit the blocks grid-stride.
-hipError_t launch_update_blocks(const UpdLaunch& a, int m, int64_t blk_base, void* stream, int grid = 0);
+// grid > 0: that many workgroups (two_per_cu: twice as many smaller ones, SGD)
+// visit the blocks grid-stride.
+hipError_t launch_update_blocks(const UpdLaunch& a, int m, int64_t blk_base, void* stream, int grid = 0,
+                                bool two_per_cu = false);
 // Caller-owned side stream and events of the overlapped path.
 struct OverlapLaunch {
   void* side;
