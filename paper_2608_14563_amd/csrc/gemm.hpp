@@ -305,11 +305,12 @@ __device__ __forceinline__ void grouped_tile(int id, int ntm, int ntn, int gm, i
 
 // A uniform value that the compiler may have computed in vector registers (an
 // integer division), in a scalar one: the copies' scalar offsets derive from it.
-// Not the builtin, which is folded away where the value is known to be uniform.
+// The empty asm hides that the value is uniform, or the builtin would be folded
+// away; the lane read itself is the builtin, so that the compiler sees it and
+// places the wait states it needs around it.
 __device__ __forceinline__ int to_scalar(int v) {
-  int s;
-  asm("v_readfirstlane_b32 %0, %1" : "=s"(s) : "v"(v));
-  return s;
+  asm("" : "+v"(v));
+  return __builtin_amdgcn_readfirstlane(v);
 }
 
 // Tile of a workgroup: ids [0, nbig) are tiles of the 256 x 256 grid (tm, tn),
