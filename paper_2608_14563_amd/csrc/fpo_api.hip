@@ -281,9 +281,10 @@ size_t carve_pg(const fpo_pg_desc& d, const PgPlan& p, void* ws, fpo::PgLaunch* 
   float* pstats = chain ? c.take<float>(d.L * 4 * d.T) : nullptr;  // per-layer, per-token norm-chain statistics
   void* dq = full ? c.take<char>(d.d_ff * p.Tp * esz) : nullptr;
   void* du = full ? c.take<char>(d.d_ff * p.Tp * esz) : nullptr;
-  // tile partials (up to four per tile): a region per matrix (3 L with the full MLP: the overlapped
-  // update reduces each matrix's partials while later launches run)
-  double* part = c.take<double>((full ? 3 * d.L : std::max<int64_t>(d.L, 2)) * 4 * p.ntiles * 3);
+  // tile partials (bf16: up to four per tile, see part_slot): a region per matrix (3 L with the
+  // full MLP: the overlapped update reduces each matrix's partials while later launches run)
+  const int64_t slots = (d.dtype == FPO_BF16 ? 4 : 1) * p.ntiles;
+  double* part = c.take<double>((full ? 3 * d.L : std::max<int64_t>(d.L, 2)) * slots * 3);
   double* up = c.take<double>(p.upd_blocks);
   double* dsq = c.take<double>(p.nmats);  // ||delta||^2 per matrix (clip-the-update mode)
   // staged bf16 pseudogradients (FPO_MODE_GRAD_BF16), one 256-aligned matrix per layer

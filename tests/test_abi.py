@@ -74,6 +74,17 @@ def test_workspace_queries_for_every_workload(lib):
     assert lib.fpo_cosine_workspace(2, n) >= 48
 
 
+def test_fp32_pseudograd_workspace_is_one_partial_a_tile(lib):
+    """fp32 tiles (64 x 64) are never cut into quarters: the workspace is the
+    transposed signal, three doubles a tile and matrix, the update's partials (one
+    a 4096 entries) and one double a matrix, each rounded up to 256 bytes."""
+    up = lambda b: -(-b // 256) * 256  # noqa: E731
+    for T, d, d_ff, n in ((2048, 4096, 12288, 64), (128, 256, 688, 2), (100, 136, 200, 3)):
+        tiles = -(-d // 64) * -(-d_ff // 64)
+        want = (up(d * (-(-T // 64) * 64) * 4) + up(n * tiles * 24) + up(n * -(-d * d_ff // 4096) * 8) + up(n * 8))
+        assert lib.fpo_pseudograd_workspace(C.byref(L.PgDesc(T, d, d_ff, n, L.FPO_F32, L.FPO_MODE_W3, 1.0))) == want
+
+
 def test_invalid_descriptions_give_zero_workspace(lib):
     assert lib.fpo_output_error_workspace(None) == 0
     assert lib.fpo_output_error_workspace(C.byref(oe(d=250))) == 0
