@@ -293,6 +293,30 @@ def test_cosine(dev, bdtype):
     assert_close("sa", float(sa[0]), O.cosine(A[0], A[0])[1], "f32")
 
 
+def test_cosine_reads_unshared_pairs_once(dev):
+    """Twelve pairs that share nothing move as many bytes as the norms of 24
+    matrices of that length (far more than the caches hold), so they may not take
+    much longer: a second read of each B would be half as many bytes again (it
+    took 1.38 times as long; 1.2 leaves the noise of a best of seven)."""
+    m = [torch.ones(1 << 24, device=dev) for _ in range(24)]
+    out = torch.empty(24, dtype=torch.float64, device=dev)
+    ws = api.workspace(api.fpo_cosine_workspace([t.numel() for t in m]), dev)
+    calls = dict(norms=lambda: api.fpo_cosine(m, sumsq_A=out, ws=ws),
+                 pairs=lambda: api.fpo_cosine(m[:12], m[12:], dot=out, ws=ws))
+    best = {}
+    for _ in range(7):
+        for name, call in calls.items():
+            call()
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(4):
+                call()
+            e[1].record()
+            torch.cuda.synchronize()
+            best[name] = min(best.get(name, 1e9), e[0].elapsed_time(e[1]))
+    assert best["pairs"] <= 1.2 * best["norms"], best
+
+
 @pytest.mark.parametrize("target", [0, 1], ids=["clip-grad", "clip-update"])
 @pytest.mark.parametrize("kind", ["sgd", "adamw", "sgd-plain"])
 @pytest.mark.parametrize("T,d,d_ff,L,clip,pffn", [(256, 256, 512, 2, 0.01, False), (300, 264, 1000, 3, 0.01, False),
