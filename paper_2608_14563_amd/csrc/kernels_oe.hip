@@ -674,40 +674,28 @@ __global__ __launch_bounds__(NT) void finalize_vjp_kernel(
     if (e_ != hipSuccess) return e_;             \
   } while (0)
 
-// One GEMM launch of the E tiles [first tile, first tile + n) (see split_tile).
-template <class E>
-static void launch_logits(const OeLaunch& a, int v0, int vc_valid, int nbv, bool fast, int n, int nbig) {
+// One GEMM launch of n workgroups (see split_tile); FAST: whole 256 x 256 tiles.
+template <class E, bool FAST>
+static void launch_logits(const OeLaunch& a, int v0, int vc_valid, int nbv, int n, int nbig) {
   using T = typename E::T;
   hipStream_t st = (hipStream_t)a.stream;
   const T* W = (const T*)a.W_U + (int64_t)v0 * a.d;
-  if (fast)
-    FPO_LAUNCH("logits_chunk", st,
-               logits_chunk_kernel<E, true><<<dim3(n), dim3(256), 0, st>>>(
-        (const T*)a.y, W, (int)a.T, (int)a.d, vc_valid, v0, a.ref, (T*)a.P, a.ldp, nbv, a.blk_m, a.blk_s, a.blk_i,
-        v0 == 0, nbig));
-  else
-    FPO_LAUNCH("logits_chunk", st,
-               logits_chunk_kernel<E, false><<<dim3(n), dim3(256), 0, st>>>(
-        (const T*)a.y, W, (int)a.T, (int)a.d, vc_valid, v0, a.ref, (T*)a.P, a.ldp, nbv, a.blk_m, a.blk_s, a.blk_i,
-        v0 == 0, nbig));
+  FPO_LAUNCH("logits_chunk", st,
+             logits_chunk_kernel<E, FAST><<<dim3(n), dim3(256), 0, st>>>(
+      (const T*)a.y, W, (int)a.T, (int)a.d, vc_valid, v0, a.ref, (T*)a.P, a.ldp, nbv, a.blk_m, a.blk_s, a.blk_i,
+      v0 == 0, nbig));
 }
 
-template <class E>
-static void launch_proj(const OeLaunch& a, int v0, int vc_valid, int nbv, bool first, bool fast, int n, int nbig) {
+template <class E, bool FAST>
+static void launch_proj(const OeLaunch& a, int v0, int vc_valid, int nbv, bool first, int n, int nbig) {
   using T = typename E::T;
   hipStream_t st = (hipStream_t)a.stream;
   const T* W = (const T*)a.W_U + (int64_t)v0 * a.d;
   const int bps = (nbv + a.nsplit - 1) / a.nsplit;
-  if (fast)
-    FPO_LAUNCH("proj_chunk", st,
-               proj_chunk_kernel<E, true><<<dim3(n), dim3(256), 0, st>>>(
-        (const T*)a.P, a.ldp, W, (int)a.T, (int)a.d, vc_valid, nbv, bps, Tile<E>::SB, first, a.nsplit, a.fout,
-        a.alpha, a.G, a.T * a.d, nbig));
-  else
-    FPO_LAUNCH("proj_chunk", st,
-               proj_chunk_kernel<E, false><<<dim3(n), dim3(256), 0, st>>>(
-        (const T*)a.P, a.ldp, W, (int)a.T, (int)a.d, vc_valid, nbv, bps, Tile<E>::SB, first, a.nsplit, a.fout,
-        a.alpha, a.G, a.T * a.d, nbig));
+  FPO_LAUNCH("proj_chunk", st,
+             proj_chunk_kernel<E, FAST><<<dim3(n), dim3(256), 0, st>>>(
+      (const T*)a.P, a.ldp, W, (int)a.T, (int)a.d, vc_valid, nbv, bps, Tile<E>::SB, first, a.nsplit, a.fout,
+      a.alpha, a.G, a.T * a.d, nbig));
 }
 
 template <class E>
@@ -740,10 +728,11 @@ static hipError_t run_output_error(const OeLaunch& a) {
         const int nbig = (int)big_tiles(a.T, vc_valid, a.d, 1).nbig;
         // whole 256 x 256 tiles and 64-deep K tiles: the copy form without bounds
         const bool fast = vc_valid % TT::BM == 0 && a.T % TT::BN == 0 && a.d % 64 == 0;
-        if (nbig) launch_logits<E>(a, (int)v0, vc_valid, nbv, fast, nbig, 0);
-        if (nbig < tiles) launch_logits<TileBF16S>(a, (int)v0, vc_valid, nbv, false, 4 * ((int)tiles - nbig), nbig);
+        if (nbig && fast) launch_logits<E, true>(a, (int)v0, vc_valid, nbv, nbig, 0);
+        else if (nbig) launch_logits<E, false>(a, (int)v0, vc_valid, nbv, nbig, 0);
+        if (nbig < tiles) launch_logits<TileBF16S, false>(a, (int)v0, vc_valid, nbv, 4 * ((int)tiles - nbig), nbig);
       } else {
-        launch_logits<E>(a, (int)v0, vc_valid, nbv, false, (int)tiles, 0);
+        launch_logits<E, false>(a, (int)v0, vc_valid, nbv, (int)tiles, 0);
       }
       FPO_CHECK_LAUNCH();
     }
@@ -757,11 +746,12 @@ static hipError_t run_output_error(const OeLaunch& a) {
       if constexpr (kBf16) {
         const int nbig = (int)big_tiles(a.T, a.d, ceil_div(nbv, a.nsplit) * TT::SB, a.nsplit, a.d).nbig;
         const bool fast = a.T % TT::BM == 0 && a.d % TT::BN == 0 && vc_valid % 64 == 0;
-        if (nbig) launch_proj<E>(a, (int)v0, vc_valid, nbv, c == 0, fast, nbig, 0);
+        if (nbig && fast) launch_proj<E, true>(a, (int)v0, vc_valid, nbv, c == 0, nbig, 0);
+        else if (nbig) launch_proj<E, false>(a, (int)v0, vc_valid, nbv, c == 0, nbig, 0);
         if (nbig < tiles)
-          launch_proj<TileBF16S>(a, (int)v0, vc_valid, nbv, c == 0, false, 4 * ((int)tiles - nbig), nbig);
+          launch_proj<TileBF16S, false>(a, (int)v0, vc_valid, nbv, c == 0, 4 * ((int)tiles - nbig), nbig);
       } else {
-        launch_proj<E>(a, (int)v0, vc_valid, nbv, c == 0, false, (int)tiles, 0);
+        launch_proj<E, false>(a, (int)v0, vc_valid, nbv, c == 0, (int)tiles, 0);
       }
       FPO_CHECK_LAUNCH();
     }

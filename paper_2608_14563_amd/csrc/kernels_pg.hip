@@ -728,18 +728,18 @@ static void launch_errh(hipStream_t st, const typename E::T* g, const typename E
   const int n = (int)pseudograd_tiles(E::BM, Tp, d_ff);
   int nbig = n;
   if constexpr (E::EPC == 8) nbig = (int)big_tiles(Tp, d_ff, d, 1, d_ff).nbig;
-  if (nbig) {
-    if (whole_tiles(T, d_ff, d))
-      FPO_LAUNCH("errh", st, errh_kernel<E, true><<<dim3(nbig), dim3(256), 0, st>>>(
-          g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T, 0));
-    else
-      FPO_LAUNCH("errh", st, errh_kernel<E, false><<<dim3(nbig), dim3(256), 0, st>>>(
-          g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T, 0));
-  }
+  auto launch = [&](auto tile, auto fast, int grid, int first) {
+    FPO_LAUNCH("errh", st, errh_kernel<decltype(tile), fast><<<dim3(grid), dim3(256), 0, st>>>(
+        g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T, first));
+  };
+  std::true_type yes;
+  std::false_type no;
   if constexpr (E::EPC == 8) {
-    if (nbig < n)
-      FPO_LAUNCH("errh", st, errh_kernel<TileBF16S, false><<<dim3(4 * (n - nbig)), dim3(256), 0, st>>>(
-          g, W3i, q, u, T, Tp, d, d_ff, dq_T, du_T, nbig));
+    if (nbig && whole_tiles(T, d_ff, d)) launch(E{}, yes, nbig, 0);
+    else if (nbig) launch(E{}, no, nbig, 0);
+    if (nbig < n) launch(TileBF16S{}, no, 4 * (n - nbig), nbig);
+  } else {
+    launch(E{}, no, n, 0);
   }
 }
 

@@ -291,14 +291,13 @@ hipError_t launch_update(const UpdLaunch& a, bool blocks) {
 // Pairs are taken in groups of consecutive ones that share A and its length (the
 // diagnostic's output cosines set one signal against every layer's gradient): a
 // workgroup loads its 4096 entries of A once and streams the group's B past them.
-constexpr int kCosBatch = kMaxMats;
 struct CosArgs {
-  const float* A[kCosBatch];      // per group
-  int64_t numel[kCosBatch];       // per group
-  int64_t gblk0[kCosBatch + 1];   // per group: first workgroup
-  int32_t first[kCosBatch + 1];   // per group: first pair
-  const void* B[kCosBatch];       // per pair
-  int64_t blk0[kCosBatch + 1];    // per pair: first block of partials
+  const float* A[kMaxMats];      // per group
+  int64_t numel[kMaxMats];       // per group
+  int64_t gblk0[kMaxMats + 1];   // per group: first workgroup
+  int32_t first[kMaxMats + 1];   // per group: first pair
+  const void* B[kMaxMats];       // per pair
+  int64_t blk0[kMaxMats + 1];    // per pair: first block of partials
 };
 
 // HBM bound: 4 or 8 bytes per element and pair. With A loaded per pair, 36 pairs
@@ -308,7 +307,7 @@ struct CosArgs {
 // Twelve unshared pairs of 33.5M: 490 us, 6.6 TB/s (of bf16 B 362 us, 6.7 TB/s).
 template <bool B16>
 __global__ __launch_bounds__(256) void cosine_kernel(CosArgs a, int n, double* __restrict__ part) {
-  __shared__ double red[kCosBatch][3][4];
+  __shared__ double red[kMaxMats][3][4];
   const int64_t b = blockIdx.x;
   const int g = find_mat(a.gblk0, n, b);
   const int64_t lb = b - a.gblk0[g];
@@ -420,52 +419,44 @@ __global__ __launch_bounds__(256) void cosine_reduce_kernel(CosArgs a, const dou
   }
 }
 
+// At most kMaxMats pairs a call: one launch carries all of them.
 hipError_t launch_cosine(const CosLaunch& a) {
   hipStream_t st = (hipStream_t)a.stream;
-  int64_t part_off = 0;
-  for (int m0 = 0; m0 < a.n; m0 += kCosBatch) {
-    const int n = std::min(kCosBatch, a.n - m0);
-    CosArgs ca{};
-    int64_t nb = 0, nwg = 0;
-    for (int k = 0; k < n; ++k) {
-      ca.B[k] = a.B[m0 + k];
-      ca.blk0[k] = nb;
-      nb += cosine_blocks(a.numel[m0 + k]);
-    }
-    ca.blk0[n] = nb;
-    int ng = 0;
-    for (int k = 0; k < n;) {
-      int run = 1;  // pairs from k on with the same A and length
-      while (k + run < n && a.A[m0 + k + run] == a.A[m0 + k] && a.numel[m0 + k + run] == a.numel[m0 + k]) ++run;
-      // at least 2048 workgroups (8 per CU) over the run before pairs are grouped:
-      // fewer leave HBM idle, and an A that small is served by the caches anyway
-      const int64_t blocks = cosine_blocks(a.numel[m0 + k]);
-      const int per = (int)std::max<int64_t>(1, std::min<int64_t>(run, run * blocks / 2048));
-      for (int q = 0; q < run; q += per) {
-        ca.A[ng] = a.A[m0 + k];
-        ca.numel[ng] = a.numel[m0 + k];
-        ca.first[ng] = k + q;
-        ca.gblk0[ng++] = nwg;
-        nwg += blocks;
-      }
-      k += run;
-    }
-    ca.first[ng] = n;
-    ca.gblk0[ng] = nwg;
-    if (a.b_bf16)
-      FPO_LAUNCH("cosine", st,
-                 cosine_kernel<true><<<dim3((unsigned)nwg), dim3(256), 0, st>>>(ca, ng, a.part + 3 * part_off));
-    else
-      FPO_LAUNCH("cosine", st,
-                 cosine_kernel<false><<<dim3((unsigned)nwg), dim3(256), 0, st>>>(ca, ng, a.part + 3 * part_off));
-    FPO_CHECK_LAUNCH();
-    FPO_LAUNCH("cosine_reduce", st,
-               cosine_reduce_kernel<<<dim3(n), dim3(256), 0, st>>>(
-        ca, a.part + 3 * part_off, a.dot ? a.dot + m0 : nullptr, a.sa ? a.sa + m0 : nullptr,
-        a.sb ? a.sb + m0 : nullptr, a.cos ? a.cos + m0 : nullptr));
-    FPO_CHECK_LAUNCH();
-    part_off += nb;
+  CosArgs ca{};
+  int64_t nb = 0, nwg = 0;
+  for (int k = 0; k < a.n; ++k) {
+    ca.B[k] = a.B[k];
+    ca.blk0[k] = nb;
+    nb += cosine_blocks(a.numel[k]);
   }
+  ca.blk0[a.n] = nb;
+  int ng = 0;
+  for (int k = 0; k < a.n;) {
+    int run = 1;  // pairs from k on with the same A and length
+    while (k + run < a.n && a.A[k + run] == a.A[k] && a.numel[k + run] == a.numel[k]) ++run;
+    // at least 2048 workgroups (8 per CU) over the run before pairs are grouped:
+    // fewer leave HBM idle, and an A that small is served by the caches anyway
+    const int64_t blocks = cosine_blocks(a.numel[k]);
+    const int per = (int)std::max<int64_t>(1, std::min<int64_t>(run, run * blocks / 2048));
+    for (int q = 0; q < run; q += per) {
+      ca.A[ng] = a.A[k];
+      ca.numel[ng] = a.numel[k];
+      ca.first[ng] = k + q;
+      ca.gblk0[ng++] = nwg;
+      nwg += blocks;
+    }
+    k += run;
+  }
+  ca.first[ng] = a.n;
+  ca.gblk0[ng] = nwg;
+  if (a.b_bf16)
+    FPO_LAUNCH("cosine", st, cosine_kernel<true><<<dim3((unsigned)nwg), dim3(256), 0, st>>>(ca, ng, a.part));
+  else
+    FPO_LAUNCH("cosine", st, cosine_kernel<false><<<dim3((unsigned)nwg), dim3(256), 0, st>>>(ca, ng, a.part));
+  FPO_CHECK_LAUNCH();
+  FPO_LAUNCH("cosine_reduce", st,
+             cosine_reduce_kernel<<<dim3(a.n), dim3(256), 0, st>>>(ca, a.part, a.dot, a.sa, a.sb, a.cos));
+  FPO_CHECK_LAUNCH();
   return hipSuccess;
 }
 
