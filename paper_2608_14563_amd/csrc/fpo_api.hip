@@ -684,7 +684,9 @@ int fpo_pseudograd(const fpo_pg_desc* desc, const void* g_tilde_lp, const void* 
   if (opt && P.bf16 && !U.clip_update && layer_macs >= (full ? 2e10 : 6e10) && (full || L > 1)) {
     fpo::OverlapLaunch ov{};
     if (overlap) ov = fpo::OverlapLaunch{overlap->side_stream, overlap->ready_event, overlap->done_event};
-    e = fpo::launch_pseudograd_update(P, U, overlap ? &ov : nullptr);
+    const fpo::FusedPlan plan = fpo::plan_fused(
+        {full, desc->T, desc->d, desc->d_ff, desc->L, stage, U.kind == fpo::kOptAdamW, U.s1[0] != nullptr});
+    e = fpo::launch_pseudograd_update(P, U, plan, overlap ? &ov : nullptr);
     if (e != hipSuccess) return hip_fail(e, "fpo_pseudograd overlapped launch");
     return FPO_OK;
   }

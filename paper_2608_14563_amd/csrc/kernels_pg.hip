@@ -827,17 +827,18 @@ static hipError_t pg_overlap_init(PgOverlap& p, int dev) {
 // beside an outer-product GEMM's on the same CUs) stream on a side stream while
 // the following launches run, with one workgroup per CU so that each CU holds
 // one GEMM workgroup and one update workgroup; the updates released by the last
-// launch have the machine to itself. With the full MLP, each layer's W1/W2 signal
-// GEMM (eq. errh) and one launch of both its W1/W2 outer products, which releases
-// both updates, come first and the W3 launches last, so that one update and not two
-// runs alone at the end (Falcon3 shapes, two layers, AdamW: 6.13 -> 5.98 ms). Same
-// per-block arithmetic and reduction order as the separate calls, so results are
-// bit-identical to them. The side stream and its two events are the caller's (ov) or, when ov is null, the device's
-// library-owned set, whose enqueue sequence is serialised by a lock.
-static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, hipStream_t side,
-                                            hipEvent_t ready_l, hipEvent_t done, int cus);
+// launch have the machine to itself. With the full MLP there are, besides the W3
+// launches, each layer's W1/W2 signal GEMM (eq. errh) and one launch of both its W1/W2
+// outer products, which releases both updates; which come first is plan_fused's
+// choice. Same per-block arithmetic and reduction order as the separate calls, so
+// results are bit-identical to them. The side stream and its two events are the
+// caller's (ov) or, when ov is null, the device's library-owned set, whose enqueue
+// sequence is serialised by a lock.
+static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, const FusedPlan& plan,
+                                            hipStream_t side, hipEvent_t ready_l, hipEvent_t done, int cus);
 
-hipError_t launch_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, const OverlapLaunch* ov) {
+hipError_t launch_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, const FusedPlan& plan,
+                                    const OverlapLaunch* ov) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -846,16 +847,16 @@ hipError_t launch_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, const
   if (ov) {
     int cus = 0;
     if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-    return enqueue_pseudograd_update(a, u, (hipStream_t)ov->side, (hipEvent_t)ov->ready, (hipEvent_t)ov->done,
-                                     cus);
+    return enqueue_pseudograd_update(a, u, plan, (hipStream_t)ov->side, (hipEvent_t)ov->ready,
+                                     (hipEvent_t)ov->done, cus);
   }
   std::lock_guard<std::mutex> lock(po.mu);
   if ((e = pg_overlap_init(po, dev)) != hipSuccess) return e;
-  return enqueue_pseudograd_update(a, u, po.side, po.ready_l, po.done, po.cus);
+  return enqueue_pseudograd_update(a, u, plan, po.side, po.ready_l, po.done, po.cus);
 }
 
-static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, hipStream_t side,
-                                            hipEvent_t ready_l, hipEvent_t done, int cus) {
+static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, const FusedPlan& plan,
+                                            hipStream_t side, hipEvent_t ready_l, hipEvent_t done, int cus) {
   hipStream_t st = (hipStream_t)a.stream;
   hipError_t e;
   if ((e = prepare_signals<uint16_t>(a, st)) != hipSuccess) return e;
@@ -900,9 +901,10 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
     if ((r = hipEventRecord(ready_l, st)) != hipSuccess) return r;
     return hipStreamWaitEvent(side, ready_l, 0);
   };
-  // full MLP: W1/W2 signals through W3_init (eq. errh), then both outer
-  // products of the layer in one launch, their updates released together
-  for (int l = 0; a.full_mlp && l < a.L; ++l) {
+  // full MLP, one layer: W1/W2 signals through W3_init (eq. errh), then both outer
+  // products in one launch, their updates released together
+  auto w12 = [&](int l, bool alone) -> hipError_t {
+    hipError_t r;
     launch_errh<TileBF16>(st, signal_rows<uint16_t>(a, l), (const uint16_t*)a.W3i[l], (const uint16_t*)a.q[l],
                           (const uint16_t*)a.u[l], (int)a.T, (int)a.Tp, (int)a.d, (int)a.d_ff, (uint16_t*)a.dq_T,
                           (uint16_t*)a.du_T);
@@ -917,12 +919,15 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
     const int slot = a.L + 2 * l;  // as many tiles as W3 (256 x 256 tiles of d x d_ff or d_ff x d)
     const int nbig = launch_outer<TileBF16>(0, 2, 2, st, oa, (int)a.d_ff, (int)a.d, (int)a.T, a.Tp, a.d, a.scale, tpart(slot));
     FPO_CHECK_LAUNCH();
-    if ((e = handoff()) != hipSuccess) return e;
-    if ((e = reduce(2, slot, nbig, a.L + l, a.L, false)) != hipSuccess) return e;
-    if ((e = update(a.L + l, false)) != hipSuccess) return e;
-    if ((e = update(2 * a.L + l, false)) != hipSuccess) return e;
-  }
-  for (int l = 0; l < a.L; ++l) {
+    if ((r = handoff()) != hipSuccess) return r;
+    if ((r = reduce(2, slot, nbig, a.L + l, a.L, false)) != hipSuccess) return r;
+    if ((r = update(a.L + l, alone)) != hipSuccess) return r;
+    return update(2 * a.L + l, alone);
+  };
+  // one layer's W3: once its tiles are complete, its norm reduction and update
+  // follow on the side stream, so the next launch starts right away
+  auto w3 = [&](int l, bool alone) -> hipError_t {
+    hipError_t r;
     OuterArgs oa{};
     oa.A[0] = signal_T<uint16_t>(a, l);
     oa.B[0] = a.a[l];
@@ -932,12 +937,17 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
     const int nbig = launch_outer<TileBF16>(l, 1, a.L, st, oa, (int)a.d, (int)a.d_ff, (int)a.T, a.Tp, a.d_ff, a.scale,
                                             tpart(l));
     FPO_CHECK_LAUNCH();
-    // layer l's tiles are complete: its norm reduction and update follow on the
-    // side stream, so the next layer's outer products start right away
-    if ((e = handoff()) != hipSuccess) return e;
-    if ((e = reduce(1, l, nbig, l, 1, true)) != hipSuccess) return e;
-    if ((e = update(l, l + 1 == a.L)) != hipSuccess) return e;
-  }
+    if ((r = handoff()) != hipSuccess) return r;
+    if ((r = reduce(1, l, nbig, l, 1, true)) != hipSuccess) return r;
+    return update(l, alone);
+  };
+  const bool w3_first = !a.full_mlp || plan.w3_first;
+  for (int l = 0; w3_first && l < a.L; ++l)
+    if ((e = w3(l, !a.full_mlp && l + 1 == a.L)) != hipSuccess) return e;
+  for (int l = 0; a.full_mlp && l < a.L; ++l)
+    if ((e = w12(l, w3_first && l + 1 == a.L)) != hipSuccess) return e;
+  for (int l = 0; !w3_first && l < a.L; ++l)
+    if ((e = w3(l, l + 1 == a.L)) != hipSuccess) return e;
   if ((e = hipEventRecord(done, side)) != hipSuccess) return e;
   if ((e = hipStreamWaitEvent(st, done, 0)) != hipSuccess) return e;
   // ||W'||^2 and the clip factors of every matrix

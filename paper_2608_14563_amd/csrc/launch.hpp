@@ -56,6 +56,43 @@ inline TileSplit big_tiles(int64_t M, int64_t N, int64_t K, int64_t mats, int64_
   return best;
 }
 
+// The fused bf16 pseudogradient + update with the gradient clip (fpo_pseudograd):
+// how its launches are laid out, from two estimates in us for one layer: `gemm`, its
+// GEMM launches on their own (big_tiles; within 5% of what a layer of a batched call
+// takes), and `upd`, one matrix's update streaming at 5.8 TB/s.
+struct FusedCase {
+  bool full;              // W1, W2 and W3, or W3 only
+  int64_t T, d, d_ff, L;
+  bool grad_bf16;         // staged in bf16
+  bool adam, state;       // state: the optimizer keeps any
+};
+struct FusedPlan {
+  bool w3_first;          // full MLP: the W3 launches before the W1/W2 ones
+  double gemm, upd;
+};
+inline FusedPlan plan_fused(const FusedCase& c) {
+  FusedPlan p{};
+  const int64_t Tp = ceil_div(c.T, 64) * 64;
+  p.gemm = big_tiles(c.d, c.d_ff, c.T, 1, c.d_ff).us;
+  if (c.full) p.gemm += big_tiles(Tp, c.d_ff, c.d, 1, c.d_ff).us + big_tiles(c.d_ff, c.d, c.T, 2, c.d).us;
+  // gradient, W read and written, its bf16 copy, state read and written
+  const int bytes = (c.grad_bf16 ? 2 : 4) + 10 + (c.adam ? 16 : c.state ? 8 : 0);
+  p.upd = (double)(c.d * c.d_ff) * bytes / 5.8e6;
+  // Overlapped full MLP, which launches come last. W3 last leaves one update without
+  // a GEMM to run beside, W1/W2 last leaves two; but W3 first releases the first
+  // update after a quarter of a layer's GEMM time, and where the updates are the
+  // longer chain that is what counts (and the two that are left have the whole
+  // machine, where beside the short W3 launches they would go at the pace of one
+  // workgroup per CU). W3 first / last, us (T, d x d_ff x L, 3 upd / gemm): AdamW 1024,
+  // 2048 x 5504 x 1 (1.08) 333 / 381; 1024, 4096 x 11008 x 2 (1.55) 2029 / 2166;
+  // SGD 256, 4096 x 11008 x 1 (2.29) 701 / 781; 2048, 2048 x 5504 x 1 (0.54) 386 / 413;
+  // 2048, 4096 x 11008 x 2 (0.66) 2280 / 2270; 3000, 4096 x 11008 x 2 (0.49) 3216 / 3095;
+  // AdamW 3000, 3072 x 23040 x 1 (0.70) 3013 / 2863; 4096, 3072 x 23040 x 2 (0.53) 5954 /
+  // 5874. Over 344 sizes the order taken is at most 3% slower than the other one.
+  p.w3_first = 3 * p.upd >= 0.75 * (p.gemm - 70.0);
+  return p;
+}
+
 struct OeLaunch {
   bool bf16;
   int64_t T, d, V, Vc;  // Vc: widest chunk, rounded up to 256
@@ -190,10 +227,11 @@ struct OverlapLaunch {
   void* ready;
   void* done;
 };
-// W3-only bf16 pseudogradients with the optimizer step overlapped (u: the
-// update of the same matrices, grad = the dW3 outputs, grad_sumsq = a.sumsq);
+// bf16 pseudogradients with the optimizer step overlapped (u: the update of the same
+// matrices, grad = the dW outputs, grad_sumsq = a.sumsq), laid out as in `plan`;
 // ov: the caller's side stream and events, or null for the library's own.
-hipError_t launch_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, const OverlapLaunch* ov);
+hipError_t launch_pseudograd_update(const PgLaunch& a, const UpdLaunch& u, const FusedPlan& plan,
+                                    const OverlapLaunch* ov);
 int64_t update_blocks(int64_t numel);
 
 struct CosLaunch {
