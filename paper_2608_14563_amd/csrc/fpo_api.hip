@@ -669,26 +669,19 @@ int fpo_pseudograd(const fpo_pg_desc* desc, const void* g_tilde_lp, const void* 
     U.stream = stream;
   }
   hipError_t e;
-  // bf16, gradient clip: each matrix's update overlaps the GEMM launches that
+  // bf16, gradient clip: each matrix's update may overlap the GEMM launches that
   // follow its outer products (clip-the-update needs every step's norm first: two
-  // passes after the pseudogradient). Worth it where a layer's GEMMs take about 100
-  // us or more: a layer on its own costs some 25 us in launches, hand-over and
-  // partly filled waves. Below, all layers' outer products go in one launch and all
-  // updates in another (same results bit for bit). T, d, d_ff, L, SGD-momentum,
-  // overlapped / batched, us: 300, 384, 1032, 3 133 / 42; 1000, 2048, 5504, 4 328 / 276;
-  // 4096, 2048, 5504, 8 1084 / 1008; 1024, 4096, 11008, 2 537 / 521; 2048, 4096,
-  // 11008, 2 633 / 669; 4096, 4096, 12288, 4 1844 / 2077; full MLP 512, 1024, 4096, 2 277 /
-  // 242; 2048, 2048, 5504, 1 404 / 417; 1024, 4096, 11008, 2 1792 / 1996. One layer's W3
-  // alone has nothing to overlap with.
-  const double layer_macs = (double)desc->T * desc->d * desc->d_ff * (full ? 4 : 1);
-  if (opt && P.bf16 && !U.clip_update && layer_macs >= (full ? 2e10 : 6e10) && (full || L > 1)) {
-    fpo::OverlapLaunch ov{};
-    if (overlap) ov = fpo::OverlapLaunch{overlap->side_stream, overlap->ready_event, overlap->done_event};
+  // passes after the pseudogradient); the results are the same bit for bit
+  if (opt && P.bf16 && !U.clip_update) {
     const fpo::FusedPlan plan = fpo::plan_fused(
         {full, desc->T, desc->d, desc->d_ff, desc->L, stage, U.kind == fpo::kOptAdamW, U.s1[0] != nullptr});
-    e = fpo::launch_pseudograd_update(P, U, plan, overlap ? &ov : nullptr);
-    if (e != hipSuccess) return hip_fail(e, "fpo_pseudograd overlapped launch");
-    return FPO_OK;
+    if (plan.overlap) {
+      fpo::OverlapLaunch ov{};
+      if (overlap) ov = fpo::OverlapLaunch{overlap->side_stream, overlap->ready_event, overlap->done_event};
+      e = fpo::launch_pseudograd_update(P, U, plan, overlap ? &ov : nullptr);
+      if (e != hipSuccess) return hip_fail(e, "fpo_pseudograd overlapped launch");
+      return FPO_OK;
+    }
   }
   // small matrices (at most 256 tile partials each): the update sums their norms
   // itself, one launch less (fp32, T = 128, 256 x 688 x 2, SGD: 33.9 -> 30.5 us)

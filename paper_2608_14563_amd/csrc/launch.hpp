@@ -67,7 +67,9 @@ struct FusedCase {
   bool adam, state;       // state: the optimizer keeps any
 };
 struct FusedPlan {
-  bool w3_first;          // full MLP: the W3 launches before the W1/W2 ones
+  bool overlap;           // each matrix's update beside the GEMM launches that follow it;
+                          // else all layers' outer products in one launch, all updates in the next
+  bool w3_first;          // overlapped full MLP: the W3 launches before the W1/W2 ones
   double gemm, upd;
 };
 inline FusedPlan plan_fused(const FusedCase& c) {
@@ -78,6 +80,42 @@ inline FusedPlan plan_fused(const FusedCase& c) {
   // gradient, W read and written, its bf16 copy, state read and written
   const int bytes = (c.grad_bf16 ? 2 : 4) + 10 + (c.adam ? 16 : c.state ? 8 : 0);
   p.upd = (double)(c.d * c.d_ff) * bytes / 5.8e6;
+  // Overlapped or batched. Batched pays gemm + upd a layer. Overlapped hides part of
+  // the shorter of the two, and pays for a launch and a hand-over a layer, partly
+  // filled waves, and the pace of the update's workgroups beside a GEMM: what it hides
+  // has to be worth that. Batched updates also find gradients that fit the 256 MB
+  // Infinity Cache there; past that size they stream from HBM (a layer's update
+  // right behind its outer products still finds them). Hence the limits, by the
+  // measured crossings: gemm at least min_gemm us (fitting or not), gemm at least
+  // min_ratio of upd, upd at least 45 us. Staged gradients are read at half the bytes
+  // and hide less; without state an update is short. Overlapped / batched, us (T, d x
+  // d_ff x L): fp32 gradients: SGD 1024, 4096 x 12288 x 6 1519 / 1805; 700, 3072 x 23040 x
+  // 16 5758 / 6504; 1024, 1536 x 8960 x 16 1227 / 1360; 700, 1536 x 8960 x 6 (gemm 30) 463 /
+  // 454; 1536, 2048 x 5504 x 4 (172 MB) 336 / 308; AdamW 2500, 1536 x 8960 x 3 (157 MB)
+  // 392 / 418; 1800, x 6 715 / 724, x 2 (105 MB) 264 / 251; staged: SGD 300, 4096 x
+  // 11008 x 8 1545 / 1654; 512, x 2 (172 MB) 442 / 436; 1024, x 8 1732 / 1999; AdamW 512,
+  // x 8 (ratio 0.36) 2374 / 2272; 1536, x 8 (0.70) 2698 / 2831; no state, 512, 3744 x
+  // 9048 x 5 618 / 594; 700, 4096 x 12288 x 6 1044 / 1110. One layer's W3 alone has
+  // nothing to overlap with.
+  struct Limits {
+    double min_gemm[2], min_ratio;  // min_gemm: gradients past the cache, within it
+  };
+  static constexpr Limits kLimits[3][2] = {
+      {{{60, 80}, 0.6}, {{75, 100}, 0.9}},    // SGD without state: fp32, staged gradients
+      {{{32, 80}, 0.3}, {{60, 100}, 0.3}},    // SGD with momentum
+      {{{40, 72}, 0.3}, {{60, 72}, 0.5}}};    // AdamW
+  const bool cached = (c.full ? 3 : 1) * c.L * c.d * c.d_ff * (c.grad_bf16 ? 2 : 4) <= ((int64_t)256 << 20);
+  if (c.full) {
+    // three updates to four GEMMs a layer: past the cache overlapped unless the
+    // matrices are small. SGD 256, 2048 x 5504 x 6 1253 / 1394; 512, 4096 x 11008 x 1 782 / 852;
+    // 2048, 4096 x 11008 x 6 6531 / 7769; 1021, 1320 x 6440 x 5 (upd 32) 1242 / 1386; 2048,
+    // 1024 x 4096 x 6 (16) 1182 / 1028; within it (129 MB) 512, 2048 x 5504 x 1 251 / 237;
+    // 2048, x 1 386 / 396; AdamW 1024, x 1 333 / 353.
+    p.overlap = p.upd >= 40.0 ? !cached || p.gemm >= 150.0 : !cached && 3 * p.upd >= 0.6 * p.gemm;
+  } else {
+    const Limits& l = kLimits[c.adam ? 2 : c.state ? 1 : 0][c.grad_bf16];
+    p.overlap = c.L > 1 && p.upd >= 45.0 && p.gemm >= l.min_gemm[cached] && p.gemm >= l.min_ratio * p.upd;
+  }
   // Overlapped full MLP, which launches come last. W3 last leaves one update without
   // a GEMM to run beside, W1/W2 last leaves two; but W3 first releases the first
   // update after a quarter of a layer's GEMM time, and where the updates are the

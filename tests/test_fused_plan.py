@@ -13,10 +13,10 @@ SRC = """
 #include "launch.hpp"
 extern "C" int plan(int full, long T, long d, long d_ff, long L, int grad_bf16, int adam, int state) {
   const fpo::FusedPlan p = fpo::plan_fused({full != 0, T, d, d_ff, L, grad_bf16 != 0, adam != 0, state != 0});
-  return p.w3_first;
+  return p.w3_first | p.overlap << 1;
 }
 """
-W3_FIRST = 1
+W3_FIRST, OVERLAP = 1, 2
 
 
 @pytest.fixture(scope="module")
@@ -49,3 +49,51 @@ def plan(tmp_path_factory):
                                              ((4096, 3072, 23040, 2, "adamw"), 5954, 5874)])
 def test_full_mlp_order(plan, case, first, last):
     assert bool(plan(True, *case) & W3_FIRST) == (first < last)
+
+
+# (T, d, d_ff, L, optimizer, staged in bf16): us overlapped, batched
+@pytest.mark.parametrize("case,overlapped,batched", [((1024, 4096, 12288, 6, "sgd", False), 1519, 1805),
+                                                     ((1024, 4096, 11008, 4, "sgd", False), 991, 1107),
+                                                     ((1024, 4096, 11008, 8, "adamw", False), 2621, 2772),
+                                                     ((1024, 4096, 11008, 8, "sgd", True), 1732, 1999),
+                                                     ((512, 4096, 11008, 8, "sgd", False), 1874, 1958),
+                                                     ((2048, 2048, 5504, 8, "adamw", False), 785, 864),
+                                                     ((2500, 1536, 8960, 3, "adamw", False), 392, 418),
+                                                     ((1024, 1536, 8960, 16, "sgd", False), 1227, 1360),
+                                                     ((1024, 4096, 12288, 6, "plain", False), 1166, 1375),
+                                                     ((700, 3072, 23040, 16, "sgd", False), 5758, 6504),
+                                                     ((4096, 1536, 8960, 3, "adamw", True), 467, 507),
+                                                     ((300, 4096, 11008, 8, "sgd", True), 1545, 1654),
+                                                     ((2048, 4096, 11008, 8, "sgd", True), 2177, 2589),
+                                                     ((300, 4096, 11008, 2, "sgd", True), 419, 404),
+                                                     ((512, 4096, 11008, 8, "adamw", True), 2374, 2272),
+                                                     ((512, 3744, 9048, 5, "plain", True), 618, 594),
+                                                     ((128, 3072, 23040, 6, "plain", True), 1275, 1197),
+                                                     ((608, 2912, 10808, 4, "adamw", True), 894, 834),
+                                                     ((1536, 2048, 5504, 4, "sgd", False), 336, 308),
+                                                     ((1800, 1536, 8960, 2, "adamw", False), 264, 251),
+                                                     ((2944, 2048, 5504, 8, "sgd", False), 884, 858),
+                                                     ((4096, 1536, 8960, 6, "plain", False), 798, 760),
+                                                     ((1024, 2048, 5504, 4, "sgd", True), 280, 264)])
+def test_w3_overlap(plan, case, overlapped, batched):
+    assert bool(plan(False, *case) & OVERLAP) == (overlapped < batched)
+
+
+def test_one_layer_of_w3_is_batched(plan):
+    assert not plan(False, 4096, 4096, 12288, 1, "sgd") & OVERLAP
+
+
+# (T, d, d_ff, L, optimizer): us overlapped (the better order), batched
+@pytest.mark.parametrize("case,overlapped,batched", [((256, 2048, 5504, 6, "sgd"), 1253, 1394),
+                                                     ((256, 4096, 11008, 1, "sgd"), 701, 763),
+                                                     ((512, 4096, 11008, 1, "sgd"), 782, 852),
+                                                     ((1024, 2048, 5504, 1, "adamw"), 333, 353),
+                                                     ((2048, 4096, 11008, 6, "sgd"), 6531, 7769),
+                                                     ((1021, 1320, 6440, 5, "sgd"), 1242, 1386),
+                                                     ((4096, 3072, 23040, 2, "adamw"), 5874, 6489),
+                                                     ((512, 1024, 4096, 2, "sgd"), 259, 231),
+                                                     ((512, 2048, 5504, 1, "sgd"), 251, 237),
+                                                     ((2048, 1024, 4096, 6, "sgd"), 1182, 1028),
+                                                     ((4096, 1024, 4096, 3, "adamw"), 943, 797)])
+def test_full_mlp_overlap(plan, case, overlapped, batched):
+    assert bool(plan(True, *case) & OVERLAP) == (overlapped < batched)
