@@ -673,8 +673,8 @@ int fpo_pseudograd(const fpo_pg_desc* desc, const void* g_tilde_lp, const void* 
   // follow its outer products (clip-the-update needs every step's norm first: two
   // passes after the pseudogradient); the results are the same bit for bit
   if (opt && P.bf16 && !U.clip_update) {
-    const fpo::FusedPlan plan = fpo::plan_fused(
-        {full, desc->T, desc->d, desc->d_ff, desc->L, stage, U.kind == fpo::kOptAdamW, U.s1[0] != nullptr});
+    const fpo::FusedPlan plan = fpo::plan_fused({full, desc->T, desc->d, desc->d_ff, desc->L, stage,
+                                                 U.kind == fpo::kOptAdamW, U.s1[0] != nullptr, ref != nullptr});
     if (plan.overlap) {
       fpo::OverlapLaunch ov{};
       if (overlap) ov = fpo::OverlapLaunch{overlap->side_stream, overlap->ready_event, overlap->done_event};

@@ -885,16 +885,8 @@ static hipError_t enqueue_pseudograd_update(const PgLaunch& a, const UpdLaunch& 
   // the update of matrix m on the side stream: one workgroup per CU beside the
   // next GEMM launch; `alone`: no GEMM follows to share the CUs, the update takes
   // the whole machine
-  // (One workgroup per CU with two blocks in flight is gentler to the GEMM, two of
-  // one block each stream faster beside it. The GEMM's time goes with T, the
-  // update's does not: below about 3000 tokens the updates are the longer chain.
-  // SGD-momentum, one / two per CU: T = 2048, 4096 x 11008 x 8 2320 / 2122 us, T =
-  // 4096, 4096 x 12288 x 4 1784 / 1790, 3072 x 23040 x 4 2659 / 2694; three per CU
-  // 2396, 1973, 2704. The full MLP has four GEMMs to three updates: T = 2048, 4096 x
-  // 11008 x 3 3355 / 3411.)
-  const bool two_per_cu = !a.full_mlp && a.T < 3072;
   auto update = [&](int m, bool alone) -> hipError_t {
-    return launch_update_blocks(u, m, blk_base[m], side, alone ? 0 : cus, two_per_cu);
+    return launch_update_blocks(u, m, blk_base[m], side, alone ? 0 : cus, plan.two_per_cu);
   };
   auto handoff = [&]() -> hipError_t {
     hipError_t r;

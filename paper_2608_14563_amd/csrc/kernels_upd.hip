@@ -181,9 +181,9 @@ hipError_t launch_update_blocks(const UpdLaunch& a, int m, int64_t blk_base, voi
   double* pt = a.part + blk_base;
   const bool adam = a.kind == kOptAdamW;
   if (loop) {
-    // one workgroup per CU: SGD two blocks per visit (124 or 140 VGPRs beside a
-    // GEMM workgroup's 328 to 344 of 512), AdamW's second moment leaves room for one.
-    // Two per CU (SGD): one block per visit, 76 VGPRs each.
+    // one workgroup per CU: SGD two blocks per visit (124 or 140 VGPRs beside a GEMM
+    // workgroup's 328 to 356 of 512), AdamW's second moment leaves room for one (116).
+    // Two per CU (SGD): one block per visit, 68 or 76 VGPRs each.
     const dim3 g((unsigned)grid);
     if (adam && a.grad_bf16)
       FPO_LAUNCH("update", st, update_loop_kernel<true, true, 1><<<g, dim3(256), 0, st>>>(ua, o, gs, ws, pt));

@@ -65,11 +65,13 @@ struct FusedCase {
   int64_t T, d, d_ff, L;
   bool grad_bf16;         // staged in bf16
   bool adam, state;       // state: the optimizer keeps any
+  bool ref;               // against reference gradients too
 };
 struct FusedPlan {
   bool overlap;           // each matrix's update beside the GEMM launches that follow it;
                           // else all layers' outer products in one launch, all updates in the next
   bool w3_first;          // overlapped full MLP: the W3 launches before the W1/W2 ones
+  bool two_per_cu;        // overlapped: two smaller update workgroups a CU instead of one
   double gemm, upd;
 };
 inline FusedPlan plan_fused(const FusedCase& c) {
@@ -113,7 +115,8 @@ inline FusedPlan plan_fused(const FusedCase& c) {
     // 2048, x 1 386 / 396; AdamW 1024, x 1 333 / 353.
     p.overlap = p.upd >= 40.0 ? !cached || p.gemm >= 150.0 : !cached && 3 * p.upd >= 0.6 * p.gemm;
   } else {
-    const Limits& l = kLimits[c.adam ? 2 : c.state ? 1 : 0][c.grad_bf16];
+    // (against references the update goes one workgroup a CU, as AdamW's does)
+    const Limits& l = kLimits[c.adam || c.ref ? 2 : c.state ? 1 : 0][c.grad_bf16];
     p.overlap = c.L > 1 && p.upd >= 45.0 && p.gemm >= l.min_gemm[cached] && p.gemm >= l.min_ratio * p.upd;
   }
   // Overlapped full MLP, which launches come last. W3 last leaves one update without
@@ -128,6 +131,22 @@ inline FusedPlan plan_fused(const FusedCase& c) {
   // AdamW 3000, 3072 x 23040 x 1 (0.70) 3013 / 2863; 4096, 3072 x 23040 x 2 (0.53) 5954 /
   // 5874. Over 344 sizes the order taken is at most 3% slower than the other one.
   p.w3_first = 3 * p.upd >= 0.75 * (p.gemm - 70.0);
+  // Overlapped W3-only SGD: two workgroups of one block each a CU stream faster beside
+  // the GEMM, one with two blocks in flight is gentler to it. The GEMM's time goes with
+  // T, the update's does not: with few tokens the updates are the longer chain. fp32
+  // gradients (twice the bytes written beside them) cross over earlier, and past 2^27
+  // entries a matrix, with state, are always better with one. Two / one, us (T, d x
+  // d_ff x L): staged, momentum 1024, 4096 x 11008 x 8 1732 / 2035; 2048, x 8 2177 / 2340;
+  // 2944, x 8 2677 / 2670; 4096, 3072 x 23040 x 6 3950 / 3929; fp32 700, 4096 x 12288 x 6 1509 /
+  // 1568; 1024, x 16 3917 / 4331; 1536, 4096 x 11008 x 8 2128 / 2158; 1800, 3072 x 23040 x 16 7379 /
+  // 6956; 1024, 8192 x 28672 x 6 7756 / 7536, without state 5624 / 5946. Three per CU
+  // took 2396 where two took 2122. AdamW's workgroup is too large for two
+  // (116 registers beside 328 to 348 of 512), and against references (a GEMM
+  // workgroup of 336 to 356) two of 76 fit at best by a few registers: 2048, 4096 x
+  // 11008 x 6 staged 2147 / 2020, 700, 4096 x 12288 x 6 fp32 1844 / 1798. The full MLP has four
+  // GEMMs to three updates: 2048, 4096 x 11008 x 4 4433 / 4391.
+  p.two_per_cu = !c.full && !c.adam && !c.ref &&
+                 c.T < (c.grad_bf16 ? 3072 : !c.state || c.d * c.d_ff < ((int64_t)1 << 27) ? 1200 : 0);
   return p;
 }
 

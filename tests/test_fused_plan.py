@@ -11,12 +11,12 @@ import pytest
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2608_14563_amd", "csrc")
 SRC = """
 #include "launch.hpp"
-extern "C" int plan(int full, long T, long d, long d_ff, long L, int grad_bf16, int adam, int state) {
-  const fpo::FusedPlan p = fpo::plan_fused({full != 0, T, d, d_ff, L, grad_bf16 != 0, adam != 0, state != 0});
-  return p.w3_first | p.overlap << 1;
+extern "C" int plan(int full, long T, long d, long d_ff, long L, int grad_bf16, int adam, int state, int ref) {
+  const fpo::FusedPlan p = fpo::plan_fused({full != 0, T, d, d_ff, L, grad_bf16 != 0, adam != 0, state != 0, ref != 0});
+  return p.w3_first | p.overlap << 1 | p.two_per_cu << 2;
 }
 """
-W3_FIRST, OVERLAP = 1, 2
+W3_FIRST, OVERLAP, TWO_PER_CU = 1, 2, 4
 
 
 @pytest.fixture(scope="module")
@@ -28,10 +28,10 @@ def plan(tmp_path_factory):
                     os.path.join(rocm, "include"), "-I", CSRC, str(d / "plan.cpp"), "-o", str(d / "plan.so")],
                    check=True)
     f = C.CDLL(str(d / "plan.so")).plan
-    f.argtypes = [C.c_int] + [C.c_long] * 4 + [C.c_int] * 3
+    f.argtypes = [C.c_int] + [C.c_long] * 4 + [C.c_int] * 4
 
-    def call(full, T, d, d_ff, L, opt, staged=False):
-        return f(full, T, d, d_ff, L, staged, opt == "adamw", opt != "plain")
+    def call(full, T, d, d_ff, L, opt, staged=False, ref=False):
+        return f(full, T, d, d_ff, L, staged, opt == "adamw", opt != "plain", ref)
 
     return call
 
@@ -97,3 +97,19 @@ def test_one_layer_of_w3_is_batched(plan):
                                                      ((4096, 1024, 4096, 3, "adamw"), 943, 797)])
 def test_full_mlp_overlap(plan, case, overlapped, batched):
     assert bool(plan(True, *case) & OVERLAP) == (overlapped < batched)
+
+
+# (T, d, d_ff, L, optimizer, staged, against references): us with two update workgroups a CU, one
+@pytest.mark.parametrize("case,two,one", [((1024, 4096, 11008, 8, "sgd", True), 1732, 2035),
+                                          ((2048, 4096, 11008, 8, "sgd", True), 2177, 2340),
+                                          ((700, 4096, 12288, 6, "sgd", False), 1509, 1568),
+                                          ((1024, 4096, 12288, 16, "sgd", False), 3917, 4331),
+                                          ((1024, 8192, 28672, 6, "plain", False), 5624, 5946),
+                                          ((1800, 3072, 23040, 16, "sgd", False), 7379, 6956),
+                                          ((1024, 8192, 28672, 6, "sgd", False), 7756, 7536),
+                                          ((4096, 3072, 23040, 6, "sgd", False), 4246, 4162),
+                                          ((2048, 4096, 11008, 6, "sgd", True, True), 2147, 2020),
+                                          ((700, 4096, 12288, 6, "sgd", False, True), 1844, 1798)])
+def test_update_workgroups_per_cu(plan, case, two, one):
+    p = plan(False, *case)
+    assert p & OVERLAP and bool(p & TWO_PER_CU) == (two < one)
