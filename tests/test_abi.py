@@ -172,7 +172,7 @@ def test_default_chunk_keeps_staged_logits_cache_sized(lib):
     for c in I.CONFIGS.values():
         dt = L.FPO_BF16 if c.dtype == "bf16" else L.FPO_F32
         esz = 2 if dt == L.FPO_BF16 else 4
-        blkw = 128 if dt == L.FPO_BF16 else 64
+        blkw = 128 if dt == L.FPO_BF16 else 32
         ws = lib.fpo_output_error_workspace(C.byref(oe(c.T, c.d, c.V, dt)))
         vc = min(budget // esz // c.T, c.V + 255)
         bound = (c.T * c.d * esz + budget + c.T * 256 + 3 * c.T * (vc // blkw + 1) * 4 + 6 * c.T * 4

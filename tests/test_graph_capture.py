@@ -1,6 +1,6 @@
 """The hot-path calls are capturable into a HIP graph (torch.cuda.CUDAGraph):
-they allocate nothing, never synchronise the host and use no memset; the
-overlapped optimizer path's side stream joins the capture through its events.
+they allocate nothing, never synchronise the host and use no memset (graphs
+of the overlapped optimizer path: tests/test_overlap_path.py).
 One SGD-momentum step (output error + pseudogradient with the fused update,
 bf16-staged) captured at step 3 is replayed three times, with eager work and
 synchronisations between replays, and every replay is bit-identical to the
@@ -19,8 +19,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("variant", ["sgd", "sgd-post-ffn", "adamw", "sgd-clip-update", "adamw-clip-update"])
 def test_step_graph_replays_match_eager(dev, variant):
-    """Overlapped path (gradient clip: SGD-momentum, with the post-FFN
-    composition, AdamW) and the two-pass clip-the-update path."""
+    """Gradient clip (SGD-momentum, with the post-FFN composition, AdamW; layers
+    this small go in one launch, all updates in the next) and the two-pass
+    clip-the-update path."""
     post_ffn = variant == "sgd-post-ffn"
     adam = variant.startswith("adamw")
     target = 1 if variant.endswith("clip-update") else 0
@@ -77,9 +78,9 @@ def test_step_graph_replays_match_eager(dev, variant):
 
 
 def test_full_mlp_step_graph_replays_match_eager(dev):
-    """The full-MLP step with the overlapped optimizer (each of the 3 L
-    matrices' norm and update released on the side stream after its outer
-    products) replays from a graph bit-identically to eager execution."""
+    """The full-MLP step with the optimizer fused (matrices this small are updated
+    in one launch after the outer products) replays from a graph bit-identically
+    to eager execution."""
     c = I.CONFIGS[1].shrink(T=256, d=256, d_ff=512, V=4104, L=2)
     x, gam, WU, y = (dev_tensor(a, dev) for a in (I.hidden(c), I.gain(c), I.unembedding(c), I.targets(c)))
     caches = [I.mlp_cache(c, l) for l in range(c.L)]

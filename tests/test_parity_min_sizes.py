@@ -80,8 +80,8 @@ def test_post_ffn_min_sizes(dev, T, d, d_ff, L):
 @pytest.mark.parametrize("target", [0, 1])
 def test_fused_update_min_sizes(dev, stage, target):
     """Two layers of 8 x 8 through the fused pseudogradient + SGD-momentum step
-    (overlapped path for the gradient clip; bf16-staged or fp32 pseudogradient)
-    against the oracle's clipped step."""
+    (bf16-staged or fp32 pseudogradient, clipping either the gradient or the
+    update) against the oracle's clipped step."""
     print(f"[min] fused update stage={stage} target={target}", flush=True)
     c = I.CONFIGS[1].shrink(T=3, d=8, d_ff=8, L=2)
     g = I.synthetic_signal(c)

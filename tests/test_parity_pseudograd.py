@@ -50,10 +50,12 @@ QUARTERS = [(1, 5, 128, 128, 1), (1, 64, 136, 120, 2), (1, 130, 8, 264, 1), (1, 
             (1, 72, 2048, 2816, 3)]
 
 
-# (1, 256, 256, 512, 2) and (1, 512, 512, 768, 3): whole tiles (copy form without bounds)
+# (1, 256, 256, 512, 2) and (1, 512, 512, 768, 3): whole tiles, few enough to go as quarters;
+# (1, 256, 2560, 2560, 1): 100 whole 256 x 256 tiles (the copy form without bounds)
 @pytest.mark.parametrize("cid,T,d,d_ff,L", [(0, 128, 256, 688, 2), (0, 300, 264, 520, 3), (1, 300, 264, 520, 2),
                                             (1, 1000, 512, 1032, 2), (1, 1, 256, 512, 1), (3, 333, 256, 1000, 2),
-                                            (1, 256, 256, 512, 2), (1, 512, 512, 768, 3)] + F32_EDGES + QUARTERS)
+                                            (1, 256, 256, 512, 2), (1, 512, 512, 768, 3),
+                                            (1, 256, 2560, 2560, 1)] + F32_EDGES + QUARTERS)
 def test_w3_outer_products(dev, cid, T, d, d_ff, L):
     c = I.CONFIGS[cid].shrink(T=T, d=d, d_ff=d_ff, L=L)
     g = signal(c)

@@ -324,13 +324,13 @@ def test_cosine_reads_unshared_pairs_once(dev):
                                                   (200, 1032, 1288, 3, 0.01, False),
                                                   (64, 64, 136, 40, 1e-3, False)])
 def test_fused_update_matches_separate_calls(dev, kind, T, d, d_ff, L, clip, pffn, target):
-    """The W3 pseudogradient with the optimizer fused (bf16: one launch per
-    layer carrying that layer's outer products and the previous layer's update)
+    """The W3 pseudogradient with the optimizer fused (layers this small: all outer
+    products in one launch, all updates in the next, which sums the norms itself)
     is bit-identical to the pseudogradient followed by fpo_apply_update, over two
     steps (momentum / moments carried), including a ragged shape, an active
     clip (clip_frac 1e-5), matrices of more update blocks than the GPU has
-    compute units (the overlapped update then visits its blocks grid-stride), and
-    more layers than one update launch takes."""
+    compute units, and more layers than one update launch takes. (The overlapped
+    path: tests/test_overlap_path.py.)"""
     c = I.CONFIGS[1].shrink(T=T, d=d, d_ff=d_ff, L=L)
     g = dev_tensor(I.synthetic_signal(c), dev)
     kw = {}
@@ -377,12 +377,12 @@ def test_fused_update_matches_separate_calls(dev, kind, T, d, d_ff, L, clip, pff
 @pytest.mark.parametrize("T,d,d_ff,L,clip", [(256, 256, 512, 2, 0.01), (300, 264, 1000, 3, 0.01),
                                              (200, 1032, 1288, 2, 1e-5)])
 def test_fused_full_mlp_update_matches_separate_calls(dev, kind, T, d, d_ff, L, clip, target):
-    """Full-MLP pseudogradient with the optimizer fused (bf16, gradient clip:
-    each matrix's update released on the side stream once its outer products
-    are done, beside the W1/W2 signal and outer-product launches that follow)
-    is bit-identical to the pseudogradient followed by fpo_apply_update over
-    the 3 L matrices (W3, W1, W2), over two steps; whole tiles, a ragged shape,
-    and matrices of more update blocks than compute units with an active clip."""
+    """Full-MLP pseudogradient with the optimizer fused (matrices this small: one
+    update launch after all outer products) is bit-identical to the
+    pseudogradient followed by fpo_apply_update over the 3 L matrices (W3, W1, W2),
+    over two steps; whole tiles, a ragged shape, and matrices of more update
+    blocks than compute units with an active clip. (The overlapped path:
+    tests/test_overlap_path.py.)"""
     c = I.CONFIGS[1].shrink(T=T, d=d, d_ff=d_ff, L=L)
     g = dev_tensor(I.synthetic_signal(c), dev)
     caches = [I.mlp_cache(c, l) for l in range(L)]

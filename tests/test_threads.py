@@ -1,8 +1,9 @@
 """Concurrent callers: two host threads, each on its own stream with its own
-buffers, run the overlapped pseudogradient + SGD-momentum step three times,
-either with the library's shared side stream (enqueue serialised by its lock)
-or each with a side stream and events of its own (fpo_overlap); each thread's
-results must equal the same steps run alone on one stream."""
+buffers, run the fused pseudogradient + SGD-momentum step three times, without
+or with a side stream and events of their own (fpo_overlap; layers this small
+go in one launch and leave them unused: tests/test_overlap_path.py has threads
+on the overlapped path); each thread's results must equal the same steps run
+alone on one stream."""
 import threading
 
 import pytest
