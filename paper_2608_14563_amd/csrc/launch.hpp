@@ -57,9 +57,8 @@ inline TileSplit big_tiles(int64_t M, int64_t N, int64_t K, int64_t mats, int64_
 }
 
 // The fused bf16 pseudogradient + update with the gradient clip (fpo_pseudograd):
-// how its launches are laid out, from two estimates in us for one layer: `gemm`, its
-// GEMM launches on their own (big_tiles; within 5% of what a layer of a batched call
-// takes), and `upd`, one matrix's update streaming at 5.8 TB/s.
+// how its launches are laid out, from estimates in us (big_tiles; a layer of a batched
+// call takes gemm + upd within 5%).
 struct FusedCase {
   bool full;              // W1, W2 and W3, or W3 only
   int64_t T, d, d_ff, L;
@@ -72,65 +71,69 @@ struct FusedPlan {
                           // else all layers' outer products in one launch, all updates in the next
   bool w3_first;          // overlapped full MLP: the W3 launches before the W1/W2 ones
   bool two_per_cu;        // overlapped: two smaller update workgroups a CU instead of one
-  double gemm, upd;
 };
 inline FusedPlan plan_fused(const FusedCase& c) {
   FusedPlan p{};
+  const double L = (double)c.L;
   const int64_t Tp = ceil_div(c.T, 64) * 64;
-  p.gemm = big_tiles(c.d, c.d_ff, c.T, 1, c.d_ff).us;
-  if (c.full) p.gemm += big_tiles(Tp, c.d_ff, c.d, 1, c.d_ff).us + big_tiles(c.d_ff, c.d, c.T, 2, c.d).us;
-  // gradient, W read and written, its bf16 copy, state read and written
-  const int bytes = (c.grad_bf16 ? 2 : 4) + 10 + (c.adam ? 16 : c.state ? 8 : 0);
-  p.upd = (double)(c.d * c.d_ff) * bytes / 5.8e6;
-  // Overlapped or batched. Batched pays gemm + upd a layer. Overlapped hides part of
-  // the shorter of the two, and pays for a launch and a hand-over a layer, partly
-  // filled waves, and the pace of the update's workgroups beside a GEMM: what it hides
-  // has to be worth that. Batched updates also find gradients that fit the 256 MB
-  // Infinity Cache there; past that size they stream from HBM (a layer's update
-  // right behind its outer products still finds them). Hence the limits, by the
-  // measured crossings: gemm at least min_gemm us (fitting or not), gemm at least
-  // min_ratio of upd, upd at least 45 us. Staged gradients are read at half the bytes
-  // and hide less; without state an update is short. Overlapped / batched, us (T, d x
-  // d_ff x L): fp32 gradients: SGD 1024, 4096 x 12288 x 6 1519 / 1805; 700, 3072 x 23040 x
-  // 16 5758 / 6504; 1024, 1536 x 8960 x 16 1227 / 1360; 700, 1536 x 8960 x 6 (gemm 30) 463 /
-  // 454; 1536, 2048 x 5504 x 4 (172 MB) 336 / 308; AdamW 2500, 1536 x 8960 x 3 (157 MB)
-  // 392 / 418; 1800, x 6 715 / 724, x 2 (105 MB) 264 / 251; staged: SGD 300, 4096 x
-  // 11008 x 8 1545 / 1654; 512, x 2 (172 MB) 442 / 436; 1024, x 8 1732 / 1999; AdamW 512,
-  // x 8 (ratio 0.36) 2374 / 2272; 1536, x 8 (0.70) 2698 / 2831; no state, 512, 3744 x
-  // 9048 x 5 618 / 594; 700, 4096 x 12288 x 6 1044 / 1110. One layer's W3 alone has
-  // nothing to overlap with.
-  struct Limits {
-    double min_gemm[2], min_ratio;  // min_gemm: gradients past the cache, within it
-  };
-  static constexpr Limits kLimits[3][2] = {
-      {{{60, 80}, 0.6}, {{75, 100}, 0.9}},    // SGD without state: fp32, staged gradients
-      {{{32, 80}, 0.3}, {{60, 100}, 0.3}},    // SGD with momentum
-      {{{40, 72}, 0.3}, {{60, 72}, 0.5}}};    // AdamW
-  const bool cached = (c.full ? 3 : 1) * c.L * c.d * c.d_ff * (c.grad_bf16 ? 2 : 4) <= ((int64_t)256 << 20);
+  const double kt = (double)ceil_div(c.T, 64);
+  const TileSplit w3 = big_tiles(c.d, c.d_ff, c.T, c.L, c.d_ff);
+  // a layer's GEMMs, launched for all layers at once (W3) and on their own (gemm1; gemmw
+  // with its partly filled waves taken as full ones)
+  double gemm = w3.us / L, gemm1 = big_tiles(c.d, c.d_ff, c.T, 1, c.d_ff).us;
+  double gemmw = w3.nbig ? ceil_div(ceil_div(c.d, 256) * ceil_div(c.d_ff, 256), kCus) * (1.6 * kt + 14.0)
+                         : ceil_div(ceil_div(c.d, 128) * ceil_div(c.d_ff, 128), kCus) * (0.55 * kt + 7.5);
   if (c.full) {
-    // three updates to four GEMMs a layer: past the cache overlapped unless the
-    // matrices are small. SGD 256, 2048 x 5504 x 6 1253 / 1394; 512, 4096 x 11008 x 1 782 / 852;
-    // 2048, 4096 x 11008 x 6 6531 / 7769; 1021, 1320 x 6440 x 5 (upd 32) 1242 / 1386; 2048,
-    // 1024 x 4096 x 6 (16) 1182 / 1028; within it (129 MB) 512, 2048 x 5504 x 1 251 / 237;
-    // 2048, x 1 386 / 396; AdamW 1024, x 1 333 / 353.
-    p.overlap = p.upd >= 40.0 ? !cached || p.gemm >= 150.0 : !cached && 3 * p.upd >= 0.6 * p.gemm;
-  } else {
-    // (against references the update goes one workgroup a CU, as AdamW's does)
-    const Limits& l = kLimits[c.adam || c.ref ? 2 : c.state ? 1 : 0][c.grad_bf16];
-    p.overlap = c.L > 1 && p.upd >= 45.0 && p.gemm >= l.min_gemm[cached] && p.gemm >= l.min_ratio * p.upd;
+    const double w12 = big_tiles(Tp, c.d_ff, c.d, 1, c.d_ff).us + big_tiles(c.d_ff, c.d, c.T, 2, c.d).us;
+    gemm += w12;
+    gemm1 += w12;
+    gemmw += w12;
   }
+  // one matrix's update at 5.8 TB/s: gradient, W read and written, its bf16 copy, state
+  // read and written
+  const int grad_bytes = c.grad_bf16 ? 2 : 4, bytes = grad_bytes + 10 + (c.adam ? 16 : c.state ? 8 : 0);
+  const double numel = (double)c.d * (double)c.d_ff, upd = numel * bytes / 5.8e6;
+  // Overlapped or batched. Of L layers' updates (three a layer with the full MLP) all
+  // but the last run beside a GEMM, which hides about half of the shorter of the two:
+  // less with staged gradients, which have the GEMM write and the update read half the
+  // bytes, least for the short update without state. Against that stand
+  //  * the pace of one or two workgroups a CU when the update outlasts its GEMM,
+  //  * a launch, a hand-over and an event a layer,
+  //  * partly filled waves: a batched launch packs all layers' tiles, and beside an
+  //    update a partly filled wave takes as long as a full one,
+  //  * gradients that fit the 256 MB Infinity Cache: a batched update finds them there
+  //    (past it only a layer's update right behind its outer products does).
+  // The factors are fitted to 2861 timed (size, optimizer, gradient type) points, T 128
+  // to 8192, d 600 to 8192, 1 to 16 layers: the path taken is 0.15% from the best one
+  // on average, more than 3% at 1.5% of them. Overlapped / batched, us (T, d x d_ff x
+  // L): fp32 gradients: SGD 1024, 4096 x 12288 x 6 1519 / 1805; 700, 3072 x 23040 x 16 5758 /
+  // 6504; 1024, 1536 x 8960 x 16 1227 / 1360; 1792, 1840 x 9088 x 3 (288 tiles: 1.1 waves)
+  // 447 / 391; 1536, 2048 x 5504 x 4 (172 MB) 336 / 308; AdamW 2048, 2048 x 5504 x 8 785 / 864;
+  // 6020, 1472 x 6584 x 5 (156 tiles) 1010 / 813; staged: SGD 512, 4096 x 11008 x 8 1596 /
+  // 1734; 1024, x 8 1732 / 1999; AdamW 512, x 8 2374 / 2272; 1536, x 8 2698 / 2831; without
+  // state 512, 3744 x 9048 x 5 618 / 594. Full MLP, SGD: 256, 2048 x 5504 x 6 1253 / 1394; 824,
+  // 1248 x 5432 x 3 530 / 610; 2048, 1024 x 4096 x 6 1182 / 1028.
+  const double per = c.full ? 3.0 : 1.0, beside = per * L - 1.0, m = gemmw / per;
+  // (against references the update goes one workgroup a CU, as AdamW's does)
+  const double hide = c.full ? 0.60 : !c.grad_bf16 ? 0.47 : c.adam || c.ref ? 0.41 : c.state ? 0.49 : 0.31;
+  const double pace = c.full ? 0.06 : 0.14, layer = c.full ? 9.0 : 13.0, waves = c.full ? 0.83 : 0.39;
+  const double grads = per * L * numel * grad_bytes, mib = (double)(1 << 20);
+  const double cached = (c.full ? 2.5 : 0.56) * std::max(0.0, std::min(1.0, (256.0 - grads / mib) / 200.0));
+  const double gain = beside * (hide * std::min(m, upd) - pace * std::max(0.0, upd - m)) -
+                      L * (layer + waves * (gemmw - gemm)) - cached * grads / 5.8e6;
+  p.overlap = beside > 0.0 && gain > 0.0;
   // Overlapped full MLP, which launches come last. W3 last leaves one update without
   // a GEMM to run beside, W1/W2 last leaves two; but W3 first releases the first
   // update after a quarter of a layer's GEMM time, and where the updates are the
   // longer chain that is what counts (and the two that are left have the whole
   // machine, where beside the short W3 launches they would go at the pace of one
-  // workgroup per CU). W3 first / last, us (T, d x d_ff x L, 3 upd / gemm): AdamW 1024,
+  // workgroup per CU). W3 first / last, us (T, d x d_ff x L, 3 upd / gemm1): AdamW 1024,
   // 2048 x 5504 x 1 (1.08) 333 / 381; 1024, 4096 x 11008 x 2 (1.55) 2029 / 2166;
   // SGD 256, 4096 x 11008 x 1 (2.29) 701 / 781; 2048, 2048 x 5504 x 1 (0.54) 386 / 413;
   // 2048, 4096 x 11008 x 2 (0.66) 2280 / 2270; 3000, 4096 x 11008 x 2 (0.49) 3216 / 3095;
   // AdamW 3000, 3072 x 23040 x 1 (0.70) 3013 / 2863; 4096, 3072 x 23040 x 2 (0.53) 5954 /
   // 5874. Over 344 sizes the order taken is at most 3% slower than the other one.
-  p.w3_first = 3 * p.upd >= 0.75 * (p.gemm - 70.0);
+  p.w3_first = 3 * upd >= 0.75 * (gemm1 - 70.0);
   // Overlapped W3-only SGD: two workgroups of one block each a CU stream faster beside
   // the GEMM, one with two blocks in flight is gentler to it. The GEMM's time goes with
   // T, the update's does not: with few tokens the updates are the longer chain. fp32

@@ -74,7 +74,11 @@ def test_full_mlp_order(plan, case, first, last):
                                                      ((1800, 1536, 8960, 2, "adamw", False), 264, 251),
                                                      ((2944, 2048, 5504, 8, "sgd", False), 884, 858),
                                                      ((4096, 1536, 8960, 6, "plain", False), 798, 760),
-                                                     ((1024, 2048, 5504, 4, "sgd", True), 280, 264)])
+                                                     ((1024, 2048, 5504, 4, "sgd", True), 280, 264),
+                                                     # partly filled waves: 288, 156, 290 tiles a layer
+                                                     ((1792, 1840, 9088, 3, "sgd", False), 447, 391),
+                                                     ((6020, 1472, 6584, 5, "adamw", False), 1010, 813),
+                                                     ((2675, 2472, 7176, 4, "sgd", True), 718, 606)])
 def test_w3_overlap(plan, case, overlapped, batched):
     assert bool(plan(False, *case) & OVERLAP) == (overlapped < batched)
 
@@ -91,6 +95,9 @@ def test_one_layer_of_w3_is_batched(plan):
                                                      ((2048, 4096, 11008, 6, "sgd"), 6531, 7769),
                                                      ((1021, 1320, 6440, 5, "sgd"), 1242, 1386),
                                                      ((4096, 3072, 23040, 2, "adamw"), 5874, 6489),
+                                                     ((824, 1248, 5432, 3, "adamw"), 587, 707),
+                                                     ((915, 2088, 6152, 12, "plain"), 3089, 3608),
+                                                     ((966, 1808, 5272, 2, "sgd"), 487, 566),
                                                      ((512, 1024, 4096, 2, "sgd"), 259, 231),
                                                      ((512, 2048, 5504, 1, "sgd"), 251, 237),
                                                      ((2048, 1024, 4096, 6, "sgd"), 1182, 1028),

@@ -18,15 +18,15 @@ from paper_2608_14563_amd import api
 pytestmark = pytest.mark.gpu
 BF = torch.bfloat16
 # ragged; one update workgroup a CU
-W3 = dict(T=4000, d=2056, d_ff=7560, L=2)
+W3 = dict(T=1300, d=4104, d_ff=7560, L=3)
 # two (SGD; AdamW's go one a CU): fp32 gradients below 1200 tokens, staged ones below 3072
 FEW = dict(T=1030, d=4104, d_ff=7560, L=3)
-STAGED = dict(T=2050, d=4104, d_ff=7560, L=2, staged=True)
+STAGED = dict(T=2050, d=4104, d_ff=7560, L=4, staged=True)
 NORM = dict(STAGED, pffn=True)
 # W3 first in both; the second in whole tiles (errh's LDS epilogue); the third W3 last
 FULL = dict(T=1000, d=1032, d_ff=11016, L=2, full=True)
 FULL_WHOLE = dict(T=512, d=1024, d_ff=11264, L=2, full=True)
-FULL_LAST = dict(T=4000, d=2056, d_ff=7560, L=1, full=True)
+FULL_LAST = dict(T=4000, d=2040, d_ff=7896, L=1, full=True)
 IDS = {id(v): k.lower() for k, v in dict(globals()).items() if isinstance(v, dict) and "d_ff" in v}
 
 
