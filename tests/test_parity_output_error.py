@@ -69,11 +69,12 @@ def test_fp32_ragged(dev, T, d, V, chunk):
     check_against_oracle(x, g, W, y, "f32", got)
 
 
-# (512, 512, 4224, 1024) and (512, 256, 2048, 0) are whole 256 x 256 tiles (the
-# GEMM core's copy form without bounds), the first with a ragged last chunk
+# (512, 512, 4224, 1024) and (512, 256, 2048, 0): whole tiles, few enough to go as quarters;
+# (2560, 2560, 4040, 2048): 80 logits and 200 projection tiles of 256 x 256, whole in the first
+# chunk (the copy forms without bounds) and ragged in the second
 @pytest.mark.parametrize("T,d,V,chunk", [(300, 264, 4104, 1024), (600, 512, 10000, 0), (256, 256, 4096, 2048), (1, 128, 1024, 0),
                                          (5, 8200, 264, 0), (16, 64, 200000, 0), (512, 512, 4224, 1024),
-                                         (512, 256, 2048, 0)])
+                                         (512, 256, 2048, 0), (2560, 2560, 4040, 2048)])
 def test_bf16_ragged(dev, T, d, V, chunk):
     c, x, g, W, y = small_case(I.CONFIGS[1], T, d, V)
     got = run_gpu(x, g, W, y, "bf16", dev, chunk=chunk)
