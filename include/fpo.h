@@ -313,10 +313,10 @@ typedef struct {
  *              optimizer path (see fpo_overlap); NULL uses the library's own
  *              (see "Library state" above)
  *   stream     the work is ordered on this stream. With opt given on the
- *              FPO_BF16 path with the gradient clip (W3 only or FULL_MLP) and
- *              layers of enough work to be worth it (else one launch carries
- *              every layer's outer products and one every update, and overlap
- *              is not used), each matrix's norm reduction and update run on the side
+ *              FPO_BF16 path with the gradient clip (W3 only or FULL_MLP),
+ *              where the library estimates it to be faster (else one launch
+ *              carries every layer's outer products and one every update, and
+ *              overlap is not used), each matrix's norm reduction and update run on the side
  *              stream once its outer products are done, overlapping the GEMM
  *              launches that follow (the next layer's outer products; with
  *              FULL_MLP the W1/W2 launches too), and are joined back to

@@ -10,8 +10,8 @@
  * extra. The registry is process-wide and guarded by a mutex.
  *
  * Kernel names: rms_forward, logits_chunk, chunk_stats, proj_chunk,
- * finalize_vjp, transpose_pad, outer, errh, reduce_parts, update,
- * update_reduce, cosine, cosine_reduce.
+ * finalize_vjp, chain_stats, signal_transpose, outer, errh, reduce_parts,
+ * update_delta, update, update_reduce, cosine, cosine_reduce.
  */
 #ifndef FPO_PROF_H
 #define FPO_PROF_H

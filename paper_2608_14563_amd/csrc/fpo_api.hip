@@ -43,8 +43,8 @@ inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 inline bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
 constexpr int64_t kIntMax = 0x7fffffff;
-// Launch geometry: the per-token kernels use one workgroup (256 lanes) per
-// token in a 1-D grid, whose lane count must stay below 2^32; the signal
+// Launch geometry: the per-token kernels use one workgroup per token (256 lanes,
+// 1024 up to 512 tokens) in a 1-D grid, whose lane count must stay below 2^32; the signal
 // transpose tiles d in 64-row steps along a grid dimension capped at 65536.
 constexpr int64_t kMaxTokens = (int64_t)1 << 23;
 constexpr int64_t kMaxHidden = (int64_t)1 << 22;

@@ -228,8 +228,9 @@ __device__ __forceinline__ void logits_epilogue_vt(const f32x16 (&acc)[4][FN], u
     int mo = 0x7fffffff;
     // after the first chunk R is the running maximum: the place of a block's
     // maximum is only read where that is above R (chunk_stats), about one block
-    // in a hundred. 512 vector instructions a wave: 0.6% of a Qwen3-8B-shaped
-    // output error (8457 -> 8408 us).
+    // in a hundred. 512 vector instructions a wave: 0.5% of a Qwen3-8B-shaped
+    // output error (8335 -> 8292 us, medians of 15 timed in turn; an OLMo-2-shaped one
+    // 2874 -> 2866).
     if (first || __any(m > R[i])) {
 #pragma unroll
       for (int f = 3; f >= 0; --f)

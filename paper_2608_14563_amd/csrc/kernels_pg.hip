@@ -2,8 +2,8 @@
 // feedback path (eq. errh):
 //   signal_transpose : g~ [T, d] -> g~^T [d, Tp] (zero columns t >= T) so that
 //                   the token axis, the contraction axis, is contiguous; with
-//                   the post-FFN composition it forms each layer's signal
-//                   (pffn_stats: its per-token norm statistics) on the way
+//                   a norm chain (post-FFN, pre-MLP) it forms each layer's signal
+//                   (chain_stats: the per-token norm statistics) on the way
 //   outer_kernel  : C_m = scale * A_m B_m for a list of matrices (MFMA),
 //                   A_m [M, Tp] token-contiguous, B_m [T, N] row-major; epilogue
 //                   writes C (fp32, or rounded to bf16 for the fused update) and
@@ -11,9 +11,9 @@
 //   errh_kernel   : E = g~ W3_init (MFMA); du = E*SiLU(q), dq = E*u*SiLU'(q),
 //                   stored token-contiguous for the W1/W2 outer products
 //   reduce_parts  : fixed-order float64 sums of the tile partials
-// With the optimizer fused (bf16), launch_pseudograd_update runs the outer
-// products one layer per launch and each matrix's update on a side stream,
-// overlapping the GEMM launches that follow.
+// With the optimizer fused (bf16) and worth overlapping (plan_fused),
+// launch_pseudograd_update runs the outer products one layer per launch and each
+// matrix's update on a side stream beside the GEMM launches that follow.
 #include "gemm.hpp"
 #include "gemm2.hpp"
 #include "gemm2s.hpp"
@@ -457,10 +457,11 @@ __device__ __forceinline__ void errh_epilogue2(const f32x16 (&acc)[FM][FN], cons
 // Tp apart: about 60 us of a 170 us tile at the OLMo-2 shapes; ragged tiles
 // still take that form.) q and u are read as 8-byte runs of the lane's 4
 // columns, kAhead fragment groups ahead of their use (1 to 4: within 1%).
-// The kernel stays at 344 registers so that an update workgroup (116 to 140) fits
-// beside it: with 64-bit addresses for every row it took all 512, the two took
-// turns on a CU, and a Falcon3-shaped full-MLP AdamW step of two layers took 5.97 ms
-// instead of 5.85 (errh alone is as fast: 0.67 ms a layer).
+// The whole-tile kernel stays at 344 registers so that an update workgroup (116 to
+// 140) fits beside it: with 64-bit addresses for every row it took all 512, the two
+// took turns on a CU, and a Falcon3-shaped full-MLP AdamW step of two layers took
+// 5.97 ms instead of 5.85 (errh alone is as fast: 0.67 ms a layer). The ragged form
+// (errh_epilogue2) still takes all 512.
 __device__ __forceinline__ void errh_epilogue_lds(f32x16 (&acc)[4][4], G2Smem& sm, int m0, int n0,
                                                   const uint16_t* __restrict__ q,
                                                   const uint16_t* __restrict__ u, int Tp,
@@ -825,8 +826,8 @@ static hipError_t pg_overlap_init(PgOverlap& p, int dev) {
 // run one layer per launch on the caller's stream; once a matrix's tiles are
 // done, its norm and update (few registers and no LDS, so its workgroups sit
 // beside an outer-product GEMM's on the same CUs) stream on a side stream while
-// the following launches run, with one workgroup per CU so that each CU holds
-// one GEMM workgroup and one update workgroup; the updates released by the last
+// the following launches run, with one workgroup per CU (or two smaller ones) so
+// that each CU holds them beside one GEMM workgroup; the updates released by the last
 // launch have the machine to itself. With the full MLP there are, besides the W3
 // launches, each layer's W1/W2 signal GEMM (eq. errh) and one launch of both its W1/W2
 // outer products, which releases both updates; which come first is plan_fused's
