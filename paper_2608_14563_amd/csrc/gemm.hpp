@@ -303,6 +303,12 @@ __device__ __forceinline__ void grouped_tile(int id, int ntm, int ntn, int gm, i
   tn = r / rows;
 }
 
+// The id that grouped_tile maps to (tm, tn).
+__device__ __forceinline__ int grouped_id(int tm, int tn, int ntm, int ntn, int gm) {
+  const int first = tm / gm * gm, rows = (ntm - first) < gm ? (ntm - first) : gm;
+  return first * ntn + tn * rows + (tm - first);
+}
+
 // A uniform value that the compiler may have computed in vector registers (an
 // integer division), in a scalar one: the copies' scalar offsets derive from it.
 // The empty asm hides that the value is uniform, or the builtin would be folded
@@ -316,13 +322,22 @@ __device__ __forceinline__ int to_scalar(int v) {
 // Tile of a workgroup: ids [0, nbig) are tiles of the 256 x 256 grid (tm, tn),
 // in a launch of their own; the grid's other tiles are taken as four 128 x 128
 // quarters each by a second launch, in whose units (tm, tn) then are (a quarter
-// may lie outside a ragged matrix).
+// may lie outside a ragged matrix). With nbig == 0 the quarters are those of the
+// qm x qn grid of 128 x 128 tiles, none outside: empty ones leave at once, but
+// the shader engines of an XCD are dealt workgroups in turn, so that with every
+// second quarter empty (at most 128 rows) half of the CUs had two of the others to
+// run one after the other. Projection, T = 64, d = 4096, V = 32000, 8 splits 68 -> 50 us;
+// logits, T = 64, d = 4096, V = 131072 281 -> 193; errh, T = 111, d = 656, d_ff = 16496 78 -> 45.
 template <bool QUARTERS>
-__device__ __forceinline__ void split_tile(int id, int nbig, int ntm, int ntn, int& tm, int& tn) {
+__device__ __forceinline__ void split_tile(int id, int nbig, int ntm, int ntn, int qm, int qn, int& tm, int& tn) {
   if constexpr (QUARTERS) {
-    grouped_tile(nbig + (id >> 2), ntm, ntn, 8, tm, tn);
-    tm = 2 * tm + (id & 1);
-    tn = 2 * tn + ((id >> 1) & 1);
+    if (nbig == 0) {
+      grouped_tile(id, qm, qn, 16, tm, tn);
+    } else {
+      grouped_tile(nbig + (id >> 2), ntm, ntn, 8, tm, tn);
+      tm = 2 * tm + (id & 1);
+      tn = 2 * tn + ((id >> 1) & 1);
+    }
   } else {
     grouped_tile(id, ntm, ntn, 8, tm, tn);
   }

@@ -307,7 +307,8 @@ __global__ __launch_bounds__(256, 1) void logits_chunk_kernel(
   const int ntm = (T + kEdge - 1) / kEdge, ntn = (vc_valid + kEdge - 1) / kEdge;
   int tm, tn;
   // consecutive workgroups share a vocabulary band and sweep the token tiles
-  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn, tm, tn);
+  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn, (T + 127) / 128, (vc_valid + 127) / 128, tm,
+                        tn);
   const int m0 = tm * TT::BM, n0 = tn * TT::BN;
   if constexpr (kQuarters) {
     if (m0 >= T || n0 >= vc_valid) return;
@@ -537,9 +538,11 @@ __global__ __launch_bounds__(256, 1) void proj_chunk_kernel(
   constexpr int kEdge = kQuarters ? 256 : TT::BM;
   // tiles: (token rows) x (split, column); columns of one split are adjacent
   const int ntm = (T + kEdge - 1) / kEdge, ntn = (d + kEdge - 1) / kEdge;
-  const int per = kQuarters ? 2 * ntn : ntn;  // column tiles of one split
+  const int qn = (d + 127) / 128;
+  const int per = !kQuarters ? ntn : nbig == 0 ? qn : 2 * ntn;  // column tiles of one split
   int tm, tsn;
-  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn * nsplit, tm, tsn);
+  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn * nsplit, (T + 127) / 128, qn * nsplit, tm,
+                        tsn);
   const int sp = to_scalar(tsn / per);
   const int m0 = tm * TT::BM, n0 = (tsn % per) * TT::BN;
   float* Gs = G + sp * split_stride;
@@ -731,7 +734,8 @@ static hipError_t run_output_error(const OeLaunch& a) {
         const bool fast = vc_valid % TT::BM == 0 && a.T % TT::BN == 0 && a.d % 64 == 0;
         if (nbig && fast) launch_logits<E, true>(a, (int)v0, vc_valid, nbv, nbig, 0);
         else if (nbig) launch_logits<E, false>(a, (int)v0, vc_valid, nbv, nbig, 0);
-        if (nbig < tiles) launch_logits<TileBF16S, false>(a, (int)v0, vc_valid, nbv, 4 * ((int)tiles - nbig), nbig);
+        if (nbig < tiles)
+          launch_logits<TileBF16S, false>(a, (int)v0, vc_valid, nbv, quarter_grid(a.T, vc_valid, 1, nbig), nbig);
       } else {
         launch_logits<E, false>(a, (int)v0, vc_valid, nbv, (int)tiles, 0);
       }
@@ -750,7 +754,8 @@ static hipError_t run_output_error(const OeLaunch& a) {
         if (nbig && fast) launch_proj<E, true>(a, (int)v0, vc_valid, nbv, c == 0, nbig, 0);
         else if (nbig) launch_proj<E, false>(a, (int)v0, vc_valid, nbv, c == 0, nbig, 0);
         if (nbig < tiles)
-          launch_proj<TileBF16S, false>(a, (int)v0, vc_valid, nbv, c == 0, 4 * ((int)tiles - nbig), nbig);
+          launch_proj<TileBF16S, false>(a, (int)v0, vc_valid, nbv, c == 0,
+                                        quarter_grid(a.T, a.d, a.nsplit, nbig), nbig);
       } else {
         launch_proj<E, false>(a, (int)v0, vc_valid, nbv, c == 0, (int)tiles, 0);
       }

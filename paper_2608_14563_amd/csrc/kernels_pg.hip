@@ -293,7 +293,7 @@ __device__ __forceinline__ void outer_epilogue2(const f32x16 (&acc)[FM][FN], con
 template <class E, bool FAST, bool REF, int OUT>
 __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, int N, int K,
                                                        int64_t lda, int64_t ldb, float scale,
-                                                       double* __restrict__ part, int nbig) {
+                                                       double* __restrict__ part, int nbig, int dense) {
   using TT = Tile<E>;
   using T = typename E::T;
   constexpr bool kQuarters = E::EPC == 8 && E::BM == 128;
@@ -308,14 +308,26 @@ __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, in
   const int ntm = (M + kEdge - 1) / kEdge, ntn = (N + kEdge - 1) / kEdge;
   const int ntiles = ntm * ntn;
   // quarters: the tiles from nbig on, four workgroups each, a contiguous range of
-  // them per XCD over the whole grid (whose tiles are then taken in order)
+  // them per XCD over the whole grid (whose tiles are then taken in order); `dense`
+  // (every tile of the list goes as quarters): only those inside the matrices, as in
+  // split_tile, in the same slots
   const int id = kQuarters ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
-  const int g = kQuarters ? nbig + (id >> 2) : id;
-  const int mat = g / ntiles, loc = g - mat * ntiles;
-  const int tile = !kQuarters || nbig > mat * ntiles ? xcd_remap(loc, ntiles) : loc;
-  int tm, tn;
-  grouped_tile(tile, ntm, ntn, 8, tm, tn);
-  const int sub = kQuarters ? id & 3 : 0;
+  int mat, g, tm, tn, sub = 0;
+  if (kQuarters && dense) {
+    const int qm = (M + 127) / 128, qn = (N + 127) / 128;
+    mat = id / (qm * qn);
+    grouped_tile(id - mat * (qm * qn), qm, qn, 16, tm, tn);
+    sub = (tm & 1) | (tn & 1) << 1;
+    tm >>= 1;
+    tn >>= 1;
+    g = mat * ntiles + grouped_id(tm, tn, ntm, ntn, 8);
+  } else {
+    g = kQuarters ? nbig + (id >> 2) : id;
+    mat = g / ntiles;
+    const int loc = g - mat * ntiles;
+    grouped_tile(!kQuarters || nbig > mat * ntiles ? xcd_remap(loc, ntiles) : loc, ntm, ntn, 8, tm, tn);
+    if (kQuarters) sub = id & 3;
+  }
   const int m0 = tm * kEdge + (sub & 1) * 128, n0 = tn * kEdge + (sub >> 1) * 128;
   const T* Am = (const T*)args.A[mat];
   const T* Bm = (const T*)args.B[mat];
@@ -324,6 +336,11 @@ __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, in
     if (m0 >= M || n0 >= N) {  // outside a ragged matrix
       if (threadIdx.x < 3) po[threadIdx.x] = 0.0;
       return;
+    }
+    // the first quarter of a tile stands in for those outside, which have no workgroup
+    if (dense && sub == 0 && threadIdx.x < 9) {
+      const int s = 1 + (int)threadIdx.x / 3;
+      if (m0 + (s & 1) * 128 >= M || n0 + (s >> 1) * 128 >= N) po[3 + threadIdx.x] = 0.0;
     }
     __shared__ G2SSmem sm;
     f32x16 acc[2][2];
@@ -554,7 +571,7 @@ __global__ __launch_bounds__(256, 1) void errh_kernel(const typename E::T* __res
   constexpr int kEdge = kQuarters ? 256 : TT::BM;
   const int ntm = (Tp + kEdge - 1) / kEdge, ntn = (d_ff + kEdge - 1) / kEdge;
   int tm, tn;
-  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn, tm, tn);
+  split_tile<kQuarters>(xcd_remap(blockIdx.x, gridDim.x), nbig, ntm, ntn, (Tp + 127) / 128, (d_ff + 127) / 128, tm, tn);
   const int m0 = tm * TT::BM, n0 = tn * TT::BN;
   if constexpr (kQuarters) {
     if (m0 >= Tp || n0 >= d_ff) return;
@@ -693,12 +710,16 @@ static int launch_outer(int m0, int mats, int of, hipStream_t st, const OuterArg
                         int64_t lda, int64_t ldb, float scale, double* part) {
   const int nt = (int)pseudograd_tiles(E::BM, M, N), n = nt * mats;
   int nbig = n;
-  if constexpr (E::EPC == 8)
-    nbig = (int)std::max<int64_t>(0, std::min<int64_t>(n, big_tiles(M, N, K, of, ldb).nbig - (int64_t)m0 * nt));
+  bool dense = false;  // of the list: the same for a matrix launched alone
+  if constexpr (E::EPC == 8) {
+    const int64_t list = big_tiles(M, N, K, of, ldb).nbig;
+    nbig = (int)std::max<int64_t>(0, std::min<int64_t>(n, list - (int64_t)m0 * nt));
+    dense = list == 0;
+  }
   auto launch = [&](auto tile, auto fast, auto with_ref, auto out, int grid) {
     using TE = decltype(tile);
     FPO_LAUNCH("outer", st, outer_kernel<TE, fast, with_ref, out><<<dim3(grid), dim3(256), 0, st>>>(
-        oa, M, N, K, lda, ldb, scale, part, nbig));
+        oa, M, N, K, lda, ldb, scale, part, nbig, dense));
   };
   std::true_type yes;
   std::false_type no;
@@ -711,7 +732,8 @@ static int launch_outer(int m0, int mats, int of, hipStream_t st, const OuterArg
         if (whole_tiles(M, N, K)) launch(E{}, yes, with_ref, out, nbig);
         else launch(E{}, no, with_ref, out, nbig);
       }
-      if (nbig < n) launch(TileBF16S{}, no, with_ref, out, 4 * (n - nbig));
+      if (nbig < n)
+        launch(TileBF16S{}, no, with_ref, out, dense ? quarter_grid(M, N, mats, 0) : 4 * (n - nbig));
     };
     // the same for all matrices of a launch
     if (oa.R[0]) oa.Cb[0] ? split(yes, bf16) : oa.C[0] ? split(yes, f32) : split(yes, none);
@@ -738,7 +760,7 @@ static void launch_errh(hipStream_t st, const typename E::T* g, const typename E
   if constexpr (E::EPC == 8) {
     if (nbig && whole_tiles(T, d_ff, d)) launch(E{}, yes, nbig, 0);
     else if (nbig) launch(E{}, no, nbig, 0);
-    if (nbig < n) launch(TileBF16S{}, no, 4 * (n - nbig), nbig);
+    if (nbig < n) launch(TileBF16S{}, no, quarter_grid(Tp, d_ff, 1, nbig), nbig);
   } else {
     launch(E{}, no, n, 0);
   }

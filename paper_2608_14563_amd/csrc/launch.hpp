@@ -56,6 +56,12 @@ inline TileSplit big_tiles(int64_t M, int64_t N, int64_t K, int64_t mats, int64_
   return best;
 }
 
+// Workgroups of the quarters launch of `mats` M x N products (split_tile).
+inline int quarter_grid(int64_t M, int64_t N, int64_t mats, int64_t nbig) {
+  if (nbig == 0) return (int)(ceil_div(M, 128) * ceil_div(N, 128) * mats);
+  return (int)(4 * (ceil_div(M, 256) * ceil_div(N, 256) * mats - nbig));
+}
+
 // The fused bf16 pseudogradient + update with the gradient clip (fpo_pseudograd):
 // how its launches are laid out, from estimates in us (big_tiles; a layer of a batched
 // call takes gemm + upd within 5%).

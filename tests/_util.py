@@ -1,9 +1,12 @@
 """Helpers shared by the GPU parity tests: moving storage arrays to the device
 and the comparison metrics of the parity contract."""
+import ctypes as C
 import math
 
 import numpy as np
 import torch
+
+from paper_2608_14563_amd import _lib as L_
 
 
 def dev_tensor(a: np.ndarray, device) -> torch.Tensor:
@@ -33,6 +36,25 @@ def cosine(x, ref) -> float:
     if nx == 0 and nr == 0:
         return 1.0
     return float(x @ ref / (nx * nr))
+
+
+def kernel_stats(name, call):
+    """(milliseconds, launches) of the library kernel `name` in one call."""
+    lib = L_.load()
+    lib.fpo_prof_enable.argtypes = [C.c_char_p]
+    lib.fpo_prof_read.argtypes = [C.c_int, C.c_char_p, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
+    names, ms, n = C.create_string_buffer(32), (C.c_double * 1)(), (C.c_int64 * 1)()
+    lib.fpo_prof_reset()
+    lib.fpo_prof_enable(name.encode())
+    call()
+    lib.fpo_prof_disable()
+    assert lib.fpo_prof_read(1, names, ms, n) == 1
+    lib.fpo_prof_reset()
+    return ms[0], n[0]
+
+
+def kernel_ms(name, call):
+    return kernel_stats(name, call)[0]
 
 
 TOL = {"f32": 1e-5, "bf16": 2e-2}

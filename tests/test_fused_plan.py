@@ -1,6 +1,7 @@
 """The layout rule of the fused pseudogradient + update (plan_fused in
 csrc/launch.hpp), compiled for the host, at sizes where the layouts it chooses
-between were timed on an MI355X and differ by more than their noise."""
+between were timed on an MI355X and differ by more than their noise; and the grid
+of a launch of quarters (quarter_grid)."""
 import ctypes as C
 import os
 import shutil
@@ -15,19 +16,25 @@ extern "C" int plan(int full, long T, long d, long d_ff, long L, int grad_bf16, 
   const fpo::FusedPlan p = fpo::plan_fused({full != 0, T, d, d_ff, L, grad_bf16 != 0, adam != 0, state != 0, ref != 0});
   return p.w3_first | p.overlap << 1 | p.two_per_cu << 2;
 }
+extern "C" int quarters(long M, long N, long mats, long nbig) { return fpo::quarter_grid(M, N, mats, nbig); }
 """
 W3_FIRST, OVERLAP, TWO_PER_CU = 1, 2, 4
 
 
 @pytest.fixture(scope="module")
-def plan(tmp_path_factory):
+def host(tmp_path_factory):
     d = tmp_path_factory.mktemp("plan")
     (d / "plan.cpp").write_text(SRC)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     subprocess.run([shutil.which("g++"), "-std=c++17", "-shared", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-I",
                     os.path.join(rocm, "include"), "-I", CSRC, str(d / "plan.cpp"), "-o", str(d / "plan.so")],
                    check=True)
-    f = C.CDLL(str(d / "plan.so")).plan
+    return C.CDLL(str(d / "plan.so"))
+
+
+@pytest.fixture(scope="module")
+def plan(host):
+    f = host.plan
     f.argtypes = [C.c_int] + [C.c_long] * 4 + [C.c_int] * 4
 
     def call(full, T, d, d_ff, L, opt, staged=False, ref=False):
@@ -120,3 +127,14 @@ def test_full_mlp_overlap(plan, case, overlapped, batched):
 def test_update_workgroups_per_cu(plan, case, two, one):
     p = plan(False, *case)
     assert p & OVERLAP and bool(p & TWO_PER_CU) == (two < one)
+
+
+@pytest.mark.parametrize("M,N,mats,nbig,want", [(64, 4096, 8, 0, 8 * 32), (130, 8, 1, 0, 2), (1, 1, 3, 0, 3),
+                                                (111, 16496, 2, 0, 2 * 129), (256, 512, 2, 0, 16),
+                                                (2048, 2816, 3, 256, 4 * 8), (300, 300, 1, 1, 12)])
+def test_quarters_have_a_workgroup_each(host, M, N, mats, nbig, want):
+    """A list that goes as quarters altogether has one workgroup per 128 x 128 tile
+    inside its matrices; the tail of a list, four per 256 x 256 tile left."""
+    f = host.quarters
+    f.argtypes = [C.c_long] * 4
+    assert f(M, N, mats, nbig) == want

@@ -6,7 +6,6 @@ norm; full MLP in whole and ragged tiles; SGD with and without momentum, AdamW),
 from two threads at once with the library's side stream or the caller's, and
 from a captured graph. Every case is checked to take that path, by the number of
 update launches."""
-import ctypes as C
 import threading
 
 import pytest
@@ -14,6 +13,7 @@ import torch
 
 from paper_2608_14563_amd import _lib as L_
 from paper_2608_14563_amd import api
+from tests._util import kernel_stats
 
 pytestmark = pytest.mark.gpu
 BF = torch.bfloat16
@@ -93,17 +93,7 @@ def same(a, b, keys=("W", "s1", "s2", "lp", "dW", "Wsq", "ss", "cs")):
 def update_launches(call):
     """Launches of the update kernel that call makes: one a matrix on the
     overlapped path, one for up to 32 matrices otherwise."""
-    lib = L_.load()
-    lib.fpo_prof_enable.argtypes = [C.c_char_p]
-    lib.fpo_prof_read.argtypes = [C.c_int, C.c_char_p, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
-    names, ms, n = C.create_string_buffer(32), (C.c_double * 1)(), (C.c_int64 * 1)()
-    lib.fpo_prof_reset()
-    lib.fpo_prof_enable(b"update")
-    call()
-    lib.fpo_prof_disable()
-    assert lib.fpo_prof_read(1, names, ms, n) == 1
-    lib.fpo_prof_reset()
-    return n[0]
+    return kernel_stats("update", call)[1]
 
 
 @pytest.mark.parametrize("case,kind", [(W3, "sgd"), (W3, "adamw"), (FEW, "sgd"), (FEW, "plain"), (FEW, "adamw"),

@@ -9,7 +9,7 @@ import torch
 import oracle as O
 from paper_2608_14563_amd import api
 from paper_2608_14563_amd import inputs as I
-from tests._util import TOL, assert_close, dev_tensor, host64
+from tests._util import TOL, assert_close, dev_tensor, host64, kernel_ms
 
 pytestmark = pytest.mark.gpu
 
@@ -101,6 +101,25 @@ def test_bf16_quarter_tiles(dev, T, d, V):
     c, x, g, W, y = small_case(I.CONFIGS[1], T, d, V)
     got = run_gpu(x, g, W, y, "bf16", dev)
     check_against_oracle(x, g, W, y, "bf16", got)
+
+
+def test_few_tokens_stream_the_unembedding(dev):
+    """64 tokens against a 1 GB unembedding: the logits are bound by reading it, and
+    take 1.28 times as long as the norm kernel does to stream as many bytes. With
+    every second workgroup of the launch empty (quarters outside the tokens) half of
+    the CUs had two of the others to run in turn: 1.87 times."""
+    T, d, V = 64, 4096, 131072
+    W = torch.randn(V, d, device=dev, dtype=torch.bfloat16)
+    x, gam = torch.randn(T, d, device=dev, dtype=torch.bfloat16), torch.ones(d, device=dev, dtype=torch.bfloat16)
+    y = torch.zeros(T, dtype=torch.int32, device=dev)
+    g, n = torch.empty(T, d, device=dev), torch.empty(1, dtype=torch.float64, device=dev)
+    ws = api.workspace(api.fpo_output_error_workspace(T, d, V, torch.bfloat16), dev)
+    A = W.view(torch.float32)
+    wsn = api.workspace(api.fpo_cosine_workspace([A.numel()]), dev)
+    A.zero_()  # finite as float32 too
+    oe = min(kernel_ms("logits_chunk", lambda: api.fpo_output_error(x, gam, W, y, g, ws=ws)) for _ in range(7))
+    norm = min(kernel_ms("cosine", lambda: api.fpo_cosine([A], sumsq_A=n, ws=wsn)) for _ in range(7))
+    assert oe <= 1.55 * norm, (oe, norm)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])

@@ -69,6 +69,27 @@ def test_w3_outer_products(dev, cid, T, d, d_ff, L):
         assert abs(got["sumsq"][l] - float((got["dW"][l] ** 2).sum())) <= 1e-5 * got["sumsq"][l]
 
 
+# lists that go as quarters altogether: one to three of a 256 x 256 tile's four inside the
+# matrix; (72, 2048, 2816, 3): 256 big tiles and eight as quarters
+@pytest.mark.parametrize("T,d,d_ff,L", [(64, 136, 120, 2), (130, 8, 264, 1), (33, 384, 128, 3), (5, 128, 640, 2),
+                                        (72, 2048, 2816, 3)])
+def test_quarters_write_every_partial(dev, T, d, d_ff, L):
+    """The norms sum a partial of every quarter of a tile, also of those outside
+    the matrix, which no workgroup computes: with NaN in the workspace before the
+    call they are the norms of the stored matrices."""
+    c = I.CONFIGS[1].shrink(T=T, d=d, d_ff=d_ff, L=L)
+    ws = api.workspace(api.fpo_pseudograd_workspace(T, d, d_ff, L, torch.bfloat16), dev)
+    ws.fill_(255)  # every double a NaN
+    dW = [torch.empty(d, d_ff, device=dev) for _ in range(L)]
+    ss = torch.empty(L, dtype=torch.float64, device=dev)
+    api.fpo_pseudograd(dev_tensor(signal(c), dev), [dev_tensor(I.activation(c, l), dev) for l in range(L)], dW3=dW,
+                       sumsq=ss, ws=ws)
+    torch.cuda.synchronize()
+    for l in range(L):
+        n = float((dW[l].double() ** 2).sum())
+        assert abs(float(ss[l]) - n) <= 1e-5 * n
+
+
 @pytest.mark.parametrize("cid", [0, 4])
 def test_fused_diagnostic_cosine(dev, cid):
     c = I.CONFIGS[cid].shrink(T=256, d=256, d_ff=512, L=3)
