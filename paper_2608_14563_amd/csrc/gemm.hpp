@@ -328,11 +328,13 @@ __device__ __forceinline__ int to_scalar(int v) {
 // second quarter empty (at most 128 rows) half of the CUs had two of the others to
 // run one after the other. Projection, T = 64, d = 4096, V = 32000, 8 splits 68 -> 50 us;
 // logits, T = 64, d = 4096, V = 131072 281 -> 193; errh, T = 111, d = 656, d_ff = 16496 78 -> 45.
+// Four rows at a time: a range of few tiles shares most panels when it is nearly
+// square (full MLP with SGD, T = 92, 408 x 1440 x 3, sixteen rows 153 to 155, four 146 to 149 us).
 template <bool QUARTERS>
 __device__ __forceinline__ void split_tile(int id, int nbig, int ntm, int ntn, int qm, int qn, int& tm, int& tn) {
   if constexpr (QUARTERS) {
     if (nbig == 0) {
-      grouped_tile(id, qm, qn, 16, tm, tn);
+      grouped_tile(id, qm, qn, 4, tm, tn);
     } else {
       grouped_tile(nbig + (id >> 2), ntm, ntn, 8, tm, tn);
       tm = 2 * tm + (id & 1);

@@ -316,7 +316,7 @@ __global__ __launch_bounds__(256, 1) void outer_kernel(OuterArgs args, int M, in
   if (kQuarters && dense) {
     const int qm = (M + 127) / 128, qn = (N + 127) / 128;
     mat = id / (qm * qn);
-    grouped_tile(id - mat * (qm * qn), qm, qn, 16, tm, tn);
+    grouped_tile(id - mat * (qm * qn), qm, qn, 4, tm, tn);
     sub = (tm & 1) | (tn & 1) << 1;
     tm >>= 1;
     tn >>= 1;
